@@ -123,13 +123,16 @@ def kernel_split(records):
     return out
 
 
-SPMM_KERNELS = ("spmm_fanin_kernel", "spmm_narrow_kernel", "spmm_slots_kernel", "spmm_tiled_kernel", "spmm_blocked_kernel")
+SPMM_KERNELS = ("spmm_fanin_kernel", "spmm_narrow_kernel", "spmm_slots_kernel", "spmm_tiled_kernel",
+                "spmm_blocked_kernel", "spmm_resident_kernel")
 
 
 def kernel_sources(kernel):
     """The library sources a kernel's counters depend on (their hash marks a counter summary as current)."""
     if kernel.startswith("spmm_blocked"):
         return ["blocked.hip", "common.h"]
+    if kernel.startswith("spmm_resident"):
+        return ["resident.hip", "common.h"]
     if kernel.startswith("gemm"):
         return ["gemm.hip", "common.h"]
     if kernel.startswith("spgemm"):

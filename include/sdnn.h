@@ -97,7 +97,8 @@ typedef struct sdnn_net_s *sdnn_net;
  * fan-out rows, the fan-in (transposed) lists, and, as n and the capacity call for them, the tile masks and
  * fp64 weight slots of near-dense layers, the window offsets of wide sparse-activation layers, the schedule
  * and staged lists of the sample-blocked product (layers wider than 16384 neurons, and from 4097 on layers
- * averaging at most 48 entries per neuron) and the dense copies; plus the set-up scratch and the per-forward
+ * averaging at most 48 entries per neuron), the interleaved lists of the LDS-resident product (up to 5119
+ * neurons) and the dense copies; plus the set-up scratch and the per-forward
  * flags.
  * Errors: NULL_POINTER, INVALID_VALUE (n, L, a capacity outside [0, 2^31-1], unknown flags).
  */
@@ -270,6 +271,8 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
  * Profiling log.  While enabled, every forward call records a pair of HIP events on the net's stream around
  * each layer's product launch(es) and around the format changes, so the log holds the GPU time of each.
  * The kernel field names what ran (SDNN_KERNEL_*); layer is the layer index, or -1 for a format change.
+ * While recording, every layer's product is a launch of its own: a range that otherwise runs as one launch
+ * (SDNN_KERNEL_RESIDENT) runs layer by layer, on the neuron-major products when a layer is small.
  * Recording costs two event records per entry and is not meant for calls under graph capture.
  */
 enum {
@@ -284,7 +287,8 @@ enum {
     SDNN_KERNEL_PACK = 8,       /* dense activations -> CSR result (sdnn_forward_csr) */
     SDNN_KERNEL_COMPACT = 9,    /* sparse rows -> CSR result (sdnn_forward_csr) */
     SDNN_KERNEL_BLOCKED = 10,   /* dense-Y CSR product on the sample-blocked layout (wide layers, short lists) */
-    SDNN_KERNEL_DENSE_GEMM32 = 11 /* dense-W arm on the fp32 matrix cores */
+    SDNN_KERNEL_DENSE_GEMM32 = 11, /* dense-W arm on the fp32 matrix cores */
+    SDNN_KERNEL_RESIDENT = 12   /* dense-Y CSR product with the activations resident in LDS (n <= 5119) */
 };
 
 typedef struct {

@@ -39,6 +39,7 @@ KERNEL_NAMES = {
     0: "transpose_kernel", 1: "spmm_fanin_kernel", 2: "spmm_narrow_kernel", 3: "spmm_slots_kernel",
     4: "spmm_tiled_kernel", 5: "gemm_dense_layer_kernel", 6: "spgemm_layer", 7: "densify", 8: "pack_dense_to_csr",
     9: "compact_rows", 10: "spmm_blocked_kernel", 11: "gemm32_dense_layer_kernel",
+    12: "spmm_resident_kernel",
 }
 
 STATUS_NAMES = {

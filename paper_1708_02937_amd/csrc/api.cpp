@@ -79,6 +79,8 @@ struct Layer {
     sdnn::BlockedSched *sched = nullptr;  // schedule of the blocked product (wide layers, short lists)
     Edge *stage = nullptr;                 // its lists in schedule order, one region per workgroup
     sdnn::BlockedRegion *regions = nullptr;  // the regions (null when one exceeds the product's LDS capacity)
+    void *resident = nullptr;    // lists interleaved for the LDS-resident product (n <= kResidentMaxN)
+    int32_t resident_blocks = 0; // its blocks of four entries per lane
     double *dense_wt = nullptr;  // n x n, W_k k-major in fp64 (zeros explicit), for the fp64 dense arm
     float *dense_wt32 = nullptr; // the same in fp32, for the fp32 dense arm
     bool dense_ready = false, dense32_ready = false;  // the dense copies hold the current W_k
@@ -100,7 +102,7 @@ constexpr size_t kAbsent = ~size_t(0);
 struct LayerPlan {
     size_t w_pack = kAbsent, fan_ptr = kAbsent, fan = kAbsent, tile_mask = kAbsent, slots = kAbsent,
            w_seg = kAbsent, sched = kAbsent, stage = kAbsent, regions = kAbsent, starts = kAbsent,
-           dense64 = kAbsent, dense32 = kAbsent;
+           resident = kAbsent, dense64 = kAbsent, dense32 = kAbsent;
     size_t bytes = 0;
 };
 
@@ -134,6 +136,7 @@ LayerPlan plan_layer(int64_t n, int64_t cap, int32_t dense_flags) {
         lp.regions = take(off, (size_t)sdnn::blocked_regions(n) * sizeof(sdnn::BlockedRegion));
         lp.starts = take(off, (size_t)(sdnn::blocked_regions(n) + 1) * sizeof(int64_t));
     }
+    if (n <= sdnn::kResidentMaxN) lp.resident = take(off, sdnn::resident_bytes(n, cap));
     if (dense_flags & SDNN_ARENA_DENSE_F64) lp.dense64 = take(off, (size_t)n * (size_t)n * sizeof(double));
     if (dense_flags & SDNN_ARENA_DENSE_F32) lp.dense32 = take(off, (size_t)n * (size_t)n * sizeof(float));
     lp.bytes = off;
@@ -296,6 +299,63 @@ bool use_blocked(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch) {
     return true;
 }
 
+// How a dense-Y range runs on the LDS-resident product: samples per workgroup, workgroups per sample group (the
+// neurons split over them), and whether the whole range is one launch.
+struct ResidentPlan {
+    int v = 0, parts = 1;
+    bool fused = true;
+};
+
+// The rule, in microseconds measured on MI355X (n 300 to 5000, 16 to 819 entries per neuron, batch 33 to 2048).
+// A workgroup takes 0.0146, 0.0173 or 0.026 us per block of 4 x 64 entries at 1, 2 or 4 samples, a CU runs one
+// workgroup at a time, a fused range costs about 3 us and 1 us per layer beyond that, and a launch per layer 4.5.
+// So few samples per workgroup where that still fills the CUs once, four where the batch does so several times
+// over, and the neurons split over workgroups (then a launch per layer) where a small batch leaves CUs idle: one
+// layer of 4096 neurons and 64 entries each at batch 64 takes 23.7 us whole and 9.2 in four parts, four layers of
+// 1024 neurons and 16 entries 11.5 us fused and 18 launch by launch.  The neuron-major products move 4 bytes
+// per product from L2 (about 27 TB/s with four samples per lane, from batch 256 on, and 12 below) and cost 6 us
+// per layer and two transposes; they win only where the last round of workgroups is nearly empty.  With profiling on every layer is a launch of its own, and ranges with a
+// layer of under 2^24 products stay on the neuron-major products: the one launch is what they gain from.
+bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, ResidentPlan *plan) {
+    const int64_t n = net->n;
+    if (n > sdnn::kResidentMaxN) return false;
+    double blocks = 0.0, gather = 2.0 * (3.0 + 8.0 * (double)n * (double)batch / 4e6);
+    for (int32_t k = k0; k < k1; ++k) {
+        const Layer &l = net->layers[(size_t)k];
+        const double products = (double)l.nnz * (double)batch;
+        if (!l.resident || (net->profiling && products < (double)(1 << 24))) return false;
+        blocks += (double)l.resident_blocks;
+        gather += 6.0 + products / (batch >= 256 && batch % 4 == 0 ? 6.75e6 : 3.0e6);
+    }
+    const int64_t runs = (n + 1023) / 1024;
+    const double layers = (double)(k1 - k0), cus = (double)net->num_cu;
+    const double per_block[] = {0.0146, 0.0173, 0.026};
+    double best = 0.0;
+    for (int i = 0; i < 3; ++i) {
+        const int v = 1 << i;
+        const double groups = (double)((batch + v - 1) / v);
+        for (int64_t parts = 1; parts <= (may_split ? runs : 1); ++parts) {
+            const double share = std::ceil((double)runs / (double)parts) / (double)runs;
+            const double rounds = std::ceil(groups * std::ceil((double)runs / std::ceil((double)runs / (double)parts)) / cus);
+            const bool fused = parts == 1 && !net->profiling;
+            const double t = rounds * blocks * share * per_block[i] + (fused ? 3.0 + layers : 4.5 * layers) +
+                             (rounds - 1.0) * layers * 0.5;
+            if (plan->v == 0 || t < best) {
+                best = t;
+                plan->v = v;
+                plan->parts = (int)parts;
+                plan->fused = fused;
+            }
+        }
+    }
+    return best <= gather;
+}
+
+bool overlap(const float *a, const float *b, size_t count) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b, bytes = count * sizeof(float);
+    return x < y + bytes && y < x + bytes;
+}
+
 hipError_t prof_event(sdnn_net net, hipEvent_t *e) {
     if (!net->ev_free.empty()) {
         *e = net->ev_free.back();
@@ -347,7 +407,8 @@ static_assert(SDNN_KERNEL_TRANSPOSE == sdnn::kKernTranspose && SDNN_KERNEL_GATHE
                   SDNN_KERNEL_TILED == sdnn::kKernTiled && SDNN_KERNEL_DENSE_GEMM == sdnn::kKernDenseGemm &&
                   SDNN_KERNEL_SPGEMM == sdnn::kKernSpgemm && SDNN_KERNEL_DENSIFY == sdnn::kKernDensify &&
                   SDNN_KERNEL_PACK == sdnn::kKernPack && SDNN_KERNEL_COMPACT == sdnn::kKernCompact &&
-                  SDNN_KERNEL_BLOCKED == sdnn::kKernBlocked && SDNN_KERNEL_DENSE_GEMM32 == sdnn::kKernDenseGemm32,
+                  SDNN_KERNEL_BLOCKED == sdnn::kKernBlocked && SDNN_KERNEL_DENSE_GEMM32 == sdnn::kKernDenseGemm32 &&
+                  SDNN_KERNEL_RESIDENT == sdnn::kKernResident,
               "profiling kernel ids of the header and the library agree");
 
 extern "C" {
@@ -500,6 +561,7 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     int64_t *starts = at<int64_t>(base, lp.starts);
     nl.tile_mask = sdnn::spmm_wants_tiles(n, nnz) ? at<uint16_t>(base, lp.tile_mask) : nullptr;
     nl.slots = sdnn::spmm_wants_slots(n, nnz) ? at<double>(base, lp.slots) : nullptr;
+    nl.resident = sdnn::resident_planned(n, nnz) ? at<void>(base, lp.resident) : nullptr;
     nl.dense_wt = at<double>(base, lp.dense64);
     nl.dense_wt32 = at<float>(base, lp.dense32);
     int32_t *counts = at<int32_t>(net->arena, net->plan.counts);
@@ -531,6 +593,10 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     }
     if (nl.tile_mask) SETUP_HIP(sdnn::launch_spmm_tile_mask(n, nl.fan_ptr, nl.fan, nl.tile_mask, s));
     if (nl.slots) SETUP_HIP(sdnn::launch_spmm_slots(n, nl.fan_ptr, nl.fan, nl.slots, s));
+    if (nl.resident) {
+        SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 2, s));
+        SETUP_HIP(hipMemcpyAsync(&nl.resident_blocks, net->d_int + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    }
     SETUP_HIP(hipStreamSynchronize(s));
 #undef SETUP_HIP
     // the product stages each workgroup's lists in LDS when the longest region fits; otherwise it reads the
@@ -594,6 +660,29 @@ sdnn_status sdnn_forward_dense_noalloc(sdnn_net net, int32_t k0, int32_t k1, int
 }
 
 int64_t sdnn_noalloc_scratch_bytes(void) { return (int64_t)kScratchBytes; }
+
+// Layers [k0, k1) on the LDS-resident product, batch-major in and out (in may equal out unless the plan splits
+// the neurons); buf: two buffers of batch x n floats for the layers between separate launches.
+static sdnn_status run_resident(sdnn_net net, int32_t k0, int32_t k1, int64_t batch, const ResidentPlan &plan,
+                                const float *in, float *out, float *const buf[2]) {
+    const int32_t step = plan.fused ? sdnn::kResidentLayers : 1;
+    for (int32_t k = k0; k < k1; k += step) {
+        sdnn::ResidentLayer rl[sdnn::kResidentLayers];
+        const int32_t count = std::min(step, k1 - k);
+        for (int32_t i = 0; i < count; ++i) {
+            const Layer &l = net->layers[(size_t)(k + i)];
+            rl[i] = sdnn::resident_layer(l.resident, net->n, l.bias);
+        }
+        float *to = k + count >= k1 ? out : buf[((k - k0) / step) & 1];
+        int pr = -1;
+        SDNN_HIP(prof_begin(net, k, sdnn::kKernResident, &pr));
+        SDNN_HIP(sdnn::launch_spmm_resident(rl, count, net->n, batch, plan.v, plan.parts, net->ymax,
+                                            net->bias_pattern, in, to, net->stream));
+        SDNN_HIP(prof_end(net, pr));
+        in = to;
+    }
+    return SDNN_OK;
+}
 
 static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int64_t batch, const float *Y_in,
                                       float *Y_out, void *ws, int64_t ws_bytes, int32_t arm, bool static_ws) {
@@ -661,6 +750,11 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         SDNN_HIP(sdnn::launch_from_blocked(n, batch, n, buf[cb], Y_out, s));
         SDNN_HIP(prof_end(net, pr));
         return SDNN_OK;
+    }
+    if (arm == SDNN_ARM_SPARSE && (Y_in == Y_out || !overlap(Y_in, Y_out, (size_t)batch * (size_t)n))) {
+        ResidentPlan plan;
+        if (plan_resident(net, k0, k1, batch, Y_in != Y_out, &plan))
+            return run_resident(net, k0, k1, batch, plan, Y_in, Y_out, buf);
     }
     SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
     SDNN_HIP(sdnn::launch_transpose(Y_in, n, buf[0], ld, batch, n, s));  // batch x n -> n x batch

@@ -27,7 +27,8 @@ enum KernelKind : int {
     kKernPack = 8,        // dense activations -> CSR result
     kKernCompact = 9,     // sparse slot rows -> CSR result
     kKernBlocked = 10,    // dense-Y product on the sample-blocked layout
-    kKernDenseGemm32 = 11 // dense-W arm on the fp32 matrix cores
+    kKernDenseGemm32 = 11,// dense-W arm on the fp32 matrix cores
+    kKernResident = 12    // dense-Y product with the activations resident in LDS
 };
 
 // Wave-local exclusive count of set bits below this lane in a 64-bit ballot.
@@ -89,6 +90,27 @@ hipError_t launch_spmm_slots(int64_t n, const int64_t *fan_ptr, const Edge *fan,
 hipError_t launch_spmm_fanin(int64_t n, int64_t batch, int64_t ld, const int64_t *fan_ptr, const Edge *fan,
                              const uint16_t *tile_mask, const double *slots, const float *bias, double ymax, int pattern,
                              const float *yt, float *zt, hipStream_t s, int *kind = nullptr);
+
+// resident.hip: the dense-Y forward with the activations of a few samples resident in LDS (batch-major in and
+// out, a range of layers per launch), for layers of at most kResidentMaxN neurons.
+constexpr int kResidentMaxN = 5119;   // two LDS buffers of n + 1 rows of four samples
+constexpr int kResidentLayers = 32;   // layers per launch
+struct ResidentLayer {
+    const char *blocks;     // interleaved lists, blocks of four entries per lane
+    const uint2 *slices;    // first block and block count of every 64-neuron slice
+    const uint16_t *order;  // neuron of every (slice, lane), 0xffff past the end
+    const float *bias;
+};
+bool resident_planned(int64_t n, int64_t nnz);     // set-up builds a layer's interleaved lists
+size_t resident_bytes(int64_t n, int64_t nnz);
+ResidentLayer resident_layer(void *mem, int64_t n, const float *bias);
+// total (device) receives the number of blocks
+hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *total,
+                                 hipStream_t s);
+// v: samples per workgroup (1, 2 or 4); parts: workgroups the neurons of a sample group are split over (one layer
+// only when above 1).  y_out may equal y_in when parts is 1.
+hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t n, int64_t batch, int v, int parts,
+                                double ymax, int pattern, const float *y_in, float *y_out, hipStream_t s);
 
 // gemm.hip
 hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s);

@@ -1,0 +1,407 @@
+// Dense-Y forward with the activations of a few samples resident in LDS (Sec. III batched inference equation;
+// Sec. IV loop body), for layers of at most 5119 neurons.
+//
+// A workgroup (16 wave64s, one per CU) owns V samples (4, 2 or 1) and keeps all n activations of them in LDS as
+// rows of V floats, one row per neuron; a lane owns one output neuron, walks its fan-in list in ascending input
+// order, reads the input's row (one LDS read of V floats) and adds the V exact products to its fp64 sums.  The
+// bias, h and the rounding follow, and the outputs form the next layer's rows in a second LDS buffer, so a whole
+// range of layers is one launch: the batch is read once, batch-major, and written once, and nothing else of it
+// touches memory.
+//
+// What bounds it: at V = 4 LDS (64 lanes reading random 16-byte rows; the LDS pipe is busy 75% of the time, two
+// thirds of that bank conflicts) and VALU issue (44 instructions per block of 4 x 64 entries, 36 of them the
+// conversions and fp64 multiply-adds) together; below that the list stream from L2.  The neuron-major gather it
+// replaces at these widths moves 4 bytes per product through the L1 from L2, and pays two transposes and a launch
+// per layer.  Measured on MI355X (before -> after): n 4096, two layers of 10%, batch 1024 490 -> 343 us; four
+// layers of 1%, batch 1021 262 -> 88 us; n 2999, six layers of 32 entries, batch 777 282 -> 82 us; n 1024, four
+// layers of 16 entries, batch 64 25.3 -> 11.5 us.  Lists two, three or four blocks ahead: 363, 352, 351 us on the
+// first of these, 80.8, 81.9, 83.2 on the third.
+//
+// Lists.  Set-up sorts each run of 1024 neurons by list length and cuts it into 16 slices of 64 (one lane per
+// neuron).  A slice holds its lists interleaved, in blocks of four entries per lane: 64 x 4 input indices of 16
+// bits, then 64 x 4 fp32 weights (1536 bytes, read with one 8-byte and one 16-byte load per lane, 6 bytes per
+// entry).  Lists are padded to their slice's longest with entries of weight 0 at input n, a row that holds
+// zeros, which leave a sum as it is.
+#include <algorithm>
+#include <atomic>
+
+#include "common.h"
+
+namespace sdnn {
+
+namespace {
+
+constexpr int kRThreads = 1024;
+constexpr int kRWaves = kRThreads / 64;
+constexpr int kRunLen = 1024;             // neurons sorted together: one slice per wave
+constexpr int kRunSlices = kRunLen / 64;
+static_assert(kRunSlices == kRWaves, "a run is one slice per wave");
+constexpr int kBlockBytes = 64 * 4 * (2 + 4);
+constexpr int kMaxLds = 160 * 1024;
+
+// ------------------------------------------------------------------------------------------ set-up
+
+// One workgroup per run: its neurons by list length (longest first, ties by index) into order[], and the blocks
+// of every slice.
+__global__ __launch_bounds__(kRunLen) void resident_order_kernel(int64_t n, const int64_t *__restrict__ fan_ptr,
+                                                                 uint16_t *__restrict__ order,
+                                                                 uint2 *__restrict__ slices) {
+    __shared__ uint32_t key[kRunLen];  // (complemented length, place in the run)
+    const int t = threadIdx.x;
+    const int64_t j = (int64_t)blockIdx.x * kRunLen + t;
+    const uint32_t len = j < n ? (uint32_t)(fan_ptr[j + 1] - fan_ptr[j]) : 0u;
+    key[t] = j < n ? ((kResidentMaxN - len) << 10 | (uint32_t)t) : 0xffffffffu;
+    __syncthreads();
+    for (int k = 2; k <= kRunLen; k <<= 1)
+        for (int d = k >> 1; d > 0; d >>= 1) {
+            const int u = t ^ d;
+            if (u > t) {
+                const uint32_t a = key[t], b = key[u];
+                if ((a > b) == ((t & k) == 0)) {
+                    key[t] = b;
+                    key[u] = a;
+                }
+            }
+            __syncthreads();
+        }
+    const uint32_t mine = key[t];
+    order[j] = mine == 0xffffffffu ? (uint16_t)0xffffu : (uint16_t)((int64_t)blockIdx.x * kRunLen + (mine & 1023u));
+    if ((t & 63) == 0)  // the slice's first list is its longest
+        slices[j / 64].y = mine == 0xffffffffu ? 0u : (kResidentMaxN - (mine >> 10) + 3u) / 4u;
+}
+
+// First block of every slice (exclusive sums of the block counts) and their total: one workgroup.
+__global__ __launch_bounds__(64) void resident_scan_kernel(int nslices, uint2 *__restrict__ slices,
+                                                           int32_t *__restrict__ total) {
+    uint32_t run = 0;
+    for (int base = 0; base < nslices; base += 64) {
+        const int s = base + (int)threadIdx.x;
+        const uint32_t c = s < nslices ? slices[s].y : 0u;
+        uint32_t incl = c;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t v = __shfl_up(incl, d);
+            if ((int)threadIdx.x >= d) incl += v;
+        }
+        if (s < nslices) slices[s].x = run + incl - c;
+        run += __shfl(incl, 63);
+    }
+    if (threadIdx.x == 0) *total = (int32_t)run;
+}
+
+// Blocks of every slice: a wave takes blocks blockIdx.y, + gridDim.y, ... of its slice.
+__global__ __launch_bounds__(64) void resident_fill_kernel(int64_t n, const int64_t *__restrict__ fan_ptr,
+                                                           const Edge *__restrict__ fan,
+                                                           const uint16_t *__restrict__ order,
+                                                           const uint2 *__restrict__ slices, char *__restrict__ blocks) {
+    const int lane = threadIdx.x;
+    const uint2 sl = slices[blockIdx.x];
+    const uint32_t j = order[(int64_t)blockIdx.x * 64 + lane];
+    int64_t e0 = 0;
+    uint32_t len = 0;
+    if (j != 0xffffu) {
+        e0 = fan_ptr[j];
+        len = (uint32_t)(fan_ptr[j + 1] - e0);
+    }
+    for (uint32_t b = blockIdx.y; b < sl.y; b += gridDim.y) {
+        uint32_t idx[4];
+        float w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            idx[u] = (uint32_t)n;
+            w[u] = 0.0f;
+            if (4 * b + u < len) {
+                const Edge e = fan[e0 + 4 * b + u];
+                idx[u] = (uint32_t)e.idx;
+                w[u] = e.w;
+            }
+        }
+        char *p = blocks + (size_t)(sl.x + b) * kBlockBytes;
+        reinterpret_cast<uint2 *>(p)[lane] = make_uint2(idx[0] | idx[1] << 16, idx[2] | idx[3] << 16);
+        reinterpret_cast<float4 *>(p + 512)[lane] = make_float4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------ product
+
+struct ResidentArgs {
+    ResidentLayer layer[kResidentLayers];
+};
+
+template <int V>
+struct RowOf;
+template <>
+struct RowOf<1> {
+    using T = float;
+};
+template <>
+struct RowOf<2> {
+    using T = float2;
+};
+template <>
+struct RowOf<4> {
+    using T = float4;
+};
+
+template <int V>
+__device__ __forceinline__ void unpack(const typename RowOf<V>::T &r, float (&y)[V]) {
+    if constexpr (V == 1) {
+        y[0] = r;
+    } else {
+        y[0] = r.x;
+        y[1] = r.y;
+        if constexpr (V == 4) {
+            y[2] = r.z;
+            y[3] = r.w;
+        }
+    }
+}
+
+template <int V>
+__device__ __forceinline__ typename RowOf<V>::T pack(const float (&y)[V]) {
+    if constexpr (V == 1)
+        return y[0];
+    else if constexpr (V == 2)
+        return make_float2(y[0], y[1]);
+    else
+        return make_float4(y[0], y[1], y[2], y[3]);
+}
+
+constexpr int kAhead = 3;  // blocks in flight per wave
+
+// A slice a wave is about to walk: its first blocks are already on their way.
+struct Slice {
+    uint32_t first, count;
+    uint32_t j;
+    uint2 i[kAhead];
+    float4 w[kAhead];
+};
+
+// grid: (sample groups, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
+// part (a single layer then) every part's workgroup reads all input rows and writes its own neurons.
+template <int V, bool kPattern>
+__global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs args, int layers, int n, int64_t batch,
+                                                                  int nslices, int runs, double ymax,
+                                                                  const float *__restrict__ y_in,
+                                                                  float *__restrict__ y_out) {
+    using Row = typename RowOf<V>::T;
+    extern __shared__ __align__(16) char resident_lds[];
+    Row *src = reinterpret_cast<Row *>(resident_lds);
+    Row *dst = src + (n + 1);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t r0 = (int64_t)blockIdx.x * V;
+    const int rows = (int)(batch - r0 < V ? batch - r0 : V);
+    const int run0 = blockIdx.y * runs;
+    const int run1 = min(run0 + runs, (nslices + kRunSlices - 1) / kRunSlices);
+    const int j0 = run0 * kRunLen;  // first neuron of the part: its outputs sit at dst[j - j0]
+
+    // slices of a run are ordered by length: a wave alternates between its ends
+    auto slice_of = [&](int run) { return run * kRunSlices + ((run & 1) ? kRunSlices - 1 - wave : wave); };
+    auto load = [&](const char *blocks, uint32_t b, uint2 &i, float4 &w) {
+        const char *p = blocks + (size_t)b * kBlockBytes;  // wave-uniform: a scalar base and 32-bit lane offsets
+        i = *reinterpret_cast<const uint2 *>(p + (uint32_t)lane * 8u);
+        w = *reinterpret_cast<const float4 *>(p + (512u + (uint32_t)lane * 16u));
+    };
+    auto fetch = [&](const ResidentLayer &l, int run, Slice &s) {
+        const int q = slice_of(run);
+        s.count = 0;
+        s.first = 0;
+        s.j = 0xffffu;
+        if (q < nslices) {
+            const uint2 d = l.slices[q];
+            s.first = __builtin_amdgcn_readfirstlane(d.x);
+            s.count = __builtin_amdgcn_readfirstlane(d.y);
+            s.j = l.order[q * 64 + lane];
+            if (s.count > 0) {
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q)
+                    load(l.blocks, s.first + min((uint32_t)q, s.count - 1), s.i[q], s.w[q]);
+            }
+        }
+    };
+
+    Slice next;
+    fetch(args.layer[0], run0, next);
+    for (int i = tid; i <= n; i += kRThreads) {
+        float y[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) y[v] = (v < rows && i < n) ? y_in[(r0 + v) * n + i] : 0.0f;
+        src[i] = pack<V>(y);
+        // both buffers end in the zero row (with several parts, dst holds one part's outputs and is never read as
+        // an input)
+        if (i == n && gridDim.y == 1) dst[i] = pack<V>(y);
+    }
+    __syncthreads();
+
+    for (int k = 0; k < layers; ++k) {
+        const ResidentLayer &l = args.layer[k];
+        for (int run = run0; run < run1; ++run) {
+            Slice cur = next;
+            // the wave's next slice, in this layer or the next, starts loading now
+            if (run + 1 < run1)
+                fetch(l, run + 1, next);
+            else if (k + 1 < layers)
+                fetch(args.layer[k + 1], run0, next);
+            const char *blocks = l.blocks;
+            const bool real = cur.j != 0xffffu;
+            const float bj = l.bias[real ? cur.j : 0];
+            double acc[V];
+            uint32_t hit[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                acc[v] = 0.0;
+                hit[v] = 0u;
+            }
+            auto block = [&](const uint2 &i, const float4 &w) {
+                const uint32_t at[4] = {i.x & 0xffffu, i.x >> 16, i.y & 0xffffu, i.y >> 16};
+                const float wv[4] = {w.x, w.y, w.z, w.w};
+                Row r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r[u] = src[at[u]];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    float y[V];
+                    unpack<V>(r[u], y);
+                    const double wd = (double)wv[u];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        acc[v] = __builtin_fma((double)y[v], wd, acc[v]);
+                        if constexpr (kPattern) hit[v] |= __float_as_uint(y[v]);
+                    }
+                }
+            };
+            // kAhead blocks are in flight; a register set is loaded again as soon as its block is used, with the
+            // last block again past the end (loaded and not used)
+            const uint32_t count = __builtin_amdgcn_readfirstlane(cur.count);
+            const uint32_t first = __builtin_amdgcn_readfirstlane(cur.first);
+            const uint32_t last = first + count - 1;
+            uint32_t b = 0;
+            for (; b + kAhead <= count; b += kAhead) {
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    block(cur.i[q], cur.w[q]);
+                    load(blocks, min(first + b + kAhead + q, last), cur.i[q], cur.w[q]);
+                    __builtin_amdgcn_sched_barrier(0);  // the load stays here, a block ahead of the next set's
+                }
+            }
+#pragma unroll
+            for (int q = 0; q + 1 < kAhead; ++q)
+                if (b + q < count) block(cur.i[q], cur.w[q]);
+            if (real) {
+                float out[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    out[v] = (kPattern && (hit[v] & 0x7fffffffu) == 0u) ? 0.0f : activate(acc[v] + (double)bj, ymax);
+                dst[(int)cur.j - j0] = pack<V>(out);
+            }
+        }
+        __syncthreads();
+        Row *t = src;
+        src = dst;
+        dst = t;
+    }
+    // the part's outputs, batch-major
+    const int count = min(n, run1 * kRunLen) - j0;
+    for (int i = tid; i < count; i += kRThreads) {
+        float y[V];
+        unpack<V>(src[i], y);
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (v < rows) y_out[(r0 + v) * n + j0 + i] = y[v];
+    }
+}
+
+int64_t resident_slices(int64_t n) { return (n + kRunLen - 1) / kRunLen * kRunSlices; }
+
+size_t lds_bytes(int64_t n, int v, int64_t out_rows) { return (size_t)(n + 1 + out_rows) * v * 4; }
+
+}  // namespace
+
+// Bytes of a layer's interleaved lists: the order and slice table, then the blocks.  Lists of a run are sorted by
+// length, so a slice's longest list is at most the shortest of the slice before it: the padding of a run is at
+// most one longest list (n entries) per lane, and the rounding to blocks of four at most a block per slice.
+size_t resident_bytes(int64_t n, int64_t nnz) {
+    const int64_t runs = (n + kRunLen - 1) / kRunLen;
+    const int64_t blocks = runs * (std::min(n, nnz) / 4 + 1 + kRunSlices) + nnz / 256 + 1;
+    return (size_t)(resident_slices(n) * (64 * 2 + 8) + 256 + blocks * kBlockBytes);
+}
+
+bool resident_planned(int64_t n, int64_t nnz) { return n <= kResidentMaxN && !spmm_wants_tiles(n, nnz); }
+
+ResidentLayer resident_layer(void *mem, int64_t n, const float *bias) {
+    ResidentLayer l;
+    char *p = static_cast<char *>(mem);
+    l.order = reinterpret_cast<uint16_t *>(p);
+    p += (resident_slices(n) * 64 * 2 + 255) / 256 * 256;
+    l.slices = reinterpret_cast<uint2 *>(p);
+    p += (resident_slices(n) * 8 + 255) / 256 * 256;
+    l.blocks = p;
+    l.bias = bias;
+    return l;
+}
+
+hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *total,
+                                 hipStream_t s) {
+    const ResidentLayer l = resident_layer(mem, n, nullptr);
+    const int64_t slices = resident_slices(n);
+    resident_order_kernel<<<(unsigned)(slices / kRunSlices), kRunLen, 0, s>>>(
+        n, fan_ptr, const_cast<uint16_t *>(l.order), const_cast<uint2 *>(l.slices));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    resident_scan_kernel<<<1, 64, 0, s>>>((int)slices, const_cast<uint2 *>(l.slices), total);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    resident_fill_kernel<<<dim3((unsigned)slices, 16), 64, 0, s>>>(n, fan_ptr, fan, l.order, l.slices,
+                                                                   const_cast<char *>(l.blocks));
+    return hipGetLastError();
+}
+
+namespace {
+
+template <int V, bool kPattern>
+hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t batch, int parts, double ymax,
+                    const float *y_in, float *y_out, hipStream_t s) {
+    const int64_t runs = (n + kRunLen - 1) / kRunLen;
+    const int per = (int)((runs + parts - 1) / parts);
+    parts = (int)((runs + per - 1) / per);
+    const size_t lds = lds_bytes(n, V, parts > 1 ? (int64_t)per * kRunLen : n + 1);
+    if (lds > (size_t)kMaxLds) return hipErrorInvalidValue;
+    // more LDS than the default dynamic limit: raised once per device (bit d; devices beyond 63 on every call)
+    static std::atomic<unsigned long long> attr_devices{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+    if (!bit || !(attr_devices.load(std::memory_order_acquire) & bit)) {
+        e = hipFuncSetAttribute((const void *)spmm_resident_kernel<V, kPattern>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+        if (e != hipSuccess) return e;
+        attr_devices.fetch_or(bit, std::memory_order_release);
+    }
+    const int64_t groups = (batch + V - 1) / V;
+    if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    spmm_resident_kernel<V, kPattern><<<dim3((unsigned)groups, (unsigned)parts), kRThreads, lds, s>>>(
+        args, layers, (int)n, batch, (int)((n + 63) / 64), per, ymax, y_in, y_out);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t n, int64_t batch, int v, int parts,
+                                double ymax, int pattern, const float *y_in, float *y_out, hipStream_t s) {
+    if (layers < 1 || layers > kResidentLayers || n > kResidentMaxN || (parts > 1 && layers > 1))
+        return hipErrorInvalidValue;
+    ResidentArgs args;
+    for (int k = 0; k < layers; ++k) args.layer[k] = layer[k];
+    switch (v * 2 + (pattern ? 1 : 0)) {
+        case 2: return launch_v<1, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 3: return launch_v<1, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 4: return launch_v<2, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 5: return launch_v<2, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 8: return launch_v<4, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 9: return launch_v<4, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace sdnn

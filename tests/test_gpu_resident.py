@@ -1,0 +1,96 @@
+"""The dense-Y forward with the activations of a few samples resident in LDS (layers of at most 5119 neurons).
+
+With the profiling log on, a range of small layers runs on the neuron-major gather instead, which sums every
+output in the same order, so the two results must be equal bit for bit; every case is also compared with the
+oracle."""
+
+import math
+
+import numpy as np
+import pytest
+
+from tests import parity
+from tests.test_gpu_parity import _mixed_length_layer
+from workloads import Problem, dense_to_csr, make_config
+
+pytestmark = pytest.mark.gpu
+
+# n around the 64-neuron slices, the 1024-neuron runs and the largest width; batches around one, two and four
+# samples per workgroup and past one round of workgroups; list lengths around the blocks of four entries
+CASES = [(1, 1, 2, [1], 0), (63, 5, 3, [0, 1, 3, 4], 0), (64, 64, 2, [5, 8, 9], 1), (65, 255, 2, [16], 0),
+         (1023, 257, 2, [0, 7, 12, 400], 0), (1024, 64, 33, [16, 2], 0), (1025, 513, 2, [4, 31], 1),
+         (2047, 1030, 1, [33, 1, 0, 90], 0), (3000, 100, 2, [20, 700, 3], 0), (4096, 64, 1, [64, 50, 0], 1),
+         (4095, 9, 3, [17, 18], 0), (5119, 255, 2, [32, 3, 48], 0), (5119, 3, 1, [2000, 1, 4], 0)]
+
+
+def _problem(n, batch, L, lengths, seed):
+    rng = np.random.default_rng(seed)
+    layers = [_mixed_length_layer(rng, n, lengths[k % len(lengths):] + lengths[:k % len(lengths)])
+              for k in range(min(L, 3))]
+    y = rng.random((batch, n), dtype=np.float32)
+    y[rng.random((batch, n)) < 0.3] = 0.0
+    return Problem(f"resident-{n}-{batch}", n, L, batch, [math.inf, 2.5][seed % 2],
+                   [layers[k % len(layers)] for k in range(L)], y0_dense=y)
+
+
+@pytest.mark.parametrize("n,batch,L,lengths,bias_mode", CASES)
+def test_resident_forward(n, batch, L, lengths, bias_mode):
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = _problem(n, batch, L, lengths, n + batch)
+    print("[case] resident", n, batch, L, bias_mode, flush=True)
+    net = sd.net_from_problem(p, bias_mode=bias_mode)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    got = net.forward_dense(y).cpu().numpy()
+    net.set_profiling(True)
+    layerwise = net.forward_dense(y).cpu().numpy()
+    net.set_profiling(False)
+    assert got.tobytes() == layerwise.tobytes()
+    if L > 1:  # in place, and in two ranges
+        z = y.clone()
+        net.forward_dense(z, out=z)
+        assert z.cpu().numpy().tobytes() == got.tobytes()
+        two = net.forward_dense(net.forward_dense(y, k0=0, k1=1), k0=1, k1=L)
+        assert two.cpu().numpy().tobytes() == got.tobytes()
+    net.free()
+    parity.compare(p, dense_to_csr(got), bias_mode=bias_mode)
+
+
+def test_resident_forward_non_finite_inputs():
+    """Infinities and NaN reach exactly the outputs whose lists hold their neuron: the list padding reads a row
+    of zeros, not another input."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = _problem(1500, 70, 1, [3, 9, 30], 5)
+    p.y0_dense[::3, ::17] = math.inf
+    p.y0_dense[1::3, ::23] = math.nan
+    p.y0_dense[:, 0] = math.inf
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    got = net.forward_dense(y).cpu().numpy()
+    net.set_profiling(True)
+    want = net.forward_dense(y).cpu().numpy()
+    net.free()
+    assert np.array_equal(got, want, equal_nan=True) and np.isfinite(got).any() and not np.isfinite(got).all()
+
+
+def test_resident_forward_named_in_profiling_log():
+    """A layer of 2^24 products or more is timed as a launch of its own under the resident kernel's name."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = make_config(2, 0.01, L=2, batch=128)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    want = net.forward_dense(y)
+    net.set_profiling(True)
+    got = net.forward_dense(y)
+    rec = net.read_profile()
+    net.free()
+    assert [(k, name) for k, name, _ in rec] == [(0, "spmm_resident_kernel"), (1, "spmm_resident_kernel")]
+    assert torch.equal(got, want)
