@@ -136,7 +136,7 @@ LayerPlan plan_layer(int64_t n, int64_t cap, int32_t dense_flags) {
         lp.regions = take(off, (size_t)sdnn::blocked_regions(n) * sizeof(sdnn::BlockedRegion));
         lp.starts = take(off, (size_t)(sdnn::blocked_regions(n) + 1) * sizeof(int64_t));
     }
-    if (n <= sdnn::kResidentMaxN) lp.resident = take(off, sdnn::resident_bytes(n, cap));
+    if (sdnn::resident_planned(n)) lp.resident = take(off, sdnn::resident_bytes(n, cap));
     if (dense_flags & SDNN_ARENA_DENSE_F64) lp.dense64 = take(off, (size_t)n * (size_t)n * sizeof(double));
     if (dense_flags & SDNN_ARENA_DENSE_F32) lp.dense32 = take(off, (size_t)n * (size_t)n * sizeof(float));
     lp.bytes = off;
@@ -316,14 +316,17 @@ struct ResidentPlan {
 // per product from L2 (about 27 TB/s with four samples per lane, from batch 256 on, and 12 below) and cost 6 us
 // per layer and two transposes; they win only where the last round of workgroups is nearly empty.  With profiling on every layer is a launch of its own, and ranges with a
 // layer of under 2^24 products stay on the neuron-major products: the one launch is what they gain from.
-bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, ResidentPlan *plan) {
+bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, bool semiring,
+                   ResidentPlan *plan) {
     const int64_t n = net->n;
     if (n > sdnn::kResidentMaxN) return false;
     double blocks = 0.0, gather = 2.0 * (3.0 + 8.0 * (double)n * (double)batch / 4e6);
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
         const double products = (double)l.nnz * (double)batch;
-        if (!l.resident || (net->profiling && products < (double)(1 << 24))) return false;
+        if (!l.resident) return false;
+        // (a semiring multiply is not logged, and high fan-in forwards have a product of their own)
+        if (!semiring && ((net->profiling && products < (double)(1 << 24)) || (l.tile_mask && batch >= 128))) return false;
         blocks += (double)l.resident_blocks;
         gather += 6.0 + products / (batch >= 256 && batch % 4 == 0 ? 6.75e6 : 3.0e6);
     }
@@ -337,7 +340,7 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
         for (int64_t parts = 1; parts <= (may_split ? runs : 1); ++parts) {
             const double share = std::ceil((double)runs / (double)parts) / (double)runs;
             const double rounds = std::ceil(groups * std::ceil((double)runs / std::ceil((double)runs / (double)parts)) / cus);
-            const bool fused = parts == 1 && !net->profiling;
+            const bool fused = parts == 1 && (semiring || !net->profiling);
             const double t = rounds * blocks * share * per_block[i] + (fused ? 3.0 + layers : 4.5 * layers) +
                              (rounds - 1.0) * layers * 0.5;
             if (plan->v == 0 || t < best) {
@@ -561,7 +564,7 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     int64_t *starts = at<int64_t>(base, lp.starts);
     nl.tile_mask = sdnn::spmm_wants_tiles(n, nnz) ? at<uint16_t>(base, lp.tile_mask) : nullptr;
     nl.slots = sdnn::spmm_wants_slots(n, nnz) ? at<double>(base, lp.slots) : nullptr;
-    nl.resident = sdnn::resident_planned(n, nnz) ? at<void>(base, lp.resident) : nullptr;
+    nl.resident = sdnn::resident_planned(n) ? at<void>(base, lp.resident) : nullptr;
     nl.dense_wt = at<double>(base, lp.dense64);
     nl.dense_wt32 = at<float>(base, lp.dense32);
     int32_t *counts = at<int32_t>(net->arena, net->plan.counts);
@@ -753,7 +756,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
     }
     if (arm == SDNN_ARM_SPARSE && (Y_in == Y_out || !overlap(Y_in, Y_out, (size_t)batch * (size_t)n))) {
         ResidentPlan plan;
-        if (plan_resident(net, k0, k1, batch, Y_in != Y_out, &plan))
+        if (plan_resident(net, k0, k1, batch, Y_in != Y_out, false, &plan))
             return run_resident(net, k0, k1, batch, plan, Y_in, Y_out, buf);
     }
     SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
@@ -1034,6 +1037,12 @@ sdnn_status sdnn_mxm_dense(sdnn_net net, int32_t k, int32_t semiring, int64_t ba
     const int64_t n = net->n;
     hipStream_t s = net->stream;
     const Layer &l = net->layers[(size_t)k];
+    ResidentPlan plan;
+    if ((Y == Z || !overlap(Y, Z, (size_t)batch * (size_t)n)) && plan_resident(net, k, k + 1, batch, Y != Z, true, &plan)) {
+        SDNN_HIP(sdnn::launch_semiring_resident(semiring, sdnn::resident_layer(l.resident, n, nullptr), n, batch, plan.v,
+                                                plan.parts, Y, Z, s));
+        return SDNN_OK;
+    }
     const int64_t ld = sdnn::act_ld(n, batch);
     float *yt = (float *)ws;
     float *zt = (float *)((char *)ws + act_bytes(n, batch));
@@ -1057,7 +1066,7 @@ sdnn_status sdnn_mxm_csr(sdnn_net net, int32_t k, int32_t semiring, int64_t batc
     const Layer &l = net->layers[(size_t)k];
     SDNN_HIP(hipMemsetAsync(net->d_flags, 0, sizeof(uint32_t), s));
     // row by row over the stored entries (the SpGEMM skeleton): Y is never densified
-    SDNN_HIP(sdnn::launch_semiring_rows(semiring, n, batch, y_row_ptr, y_col, y_val, l.row_ptr, l.w_pack, Z,
+    SDNN_HIP(sdnn::launch_semiring_rows(semiring, n, batch, l.nnz, y_row_ptr, y_col, y_val, l.row_ptr, l.w_pack, Z,
                                         net->d_flags, s));
     uint32_t flags = 0;
     SDNN_HIP(hipMemcpyAsync(&flags, net->d_flags, sizeof(uint32_t), hipMemcpyDeviceToHost, s));

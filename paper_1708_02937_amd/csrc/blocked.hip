@@ -21,8 +21,6 @@
 // chunk is read from the Infinity Cache.
 #include <algorithm>
 
-#include <atomic>
-
 #include "common.h"
 
 namespace sdnn {
@@ -803,19 +801,9 @@ hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int3
     if (e != hipSuccess) return e;
     e = launch_exclusive_scan_i32_to_i64(batch, cnt, row_ptr, scan_tmp, s);
     if (e != hipSuccess) return e;
-    // the pack's LDS exceeds the default dynamic limit: raise it once per device (bit d of attr_devices;
-    // devices beyond 63 set it on every call)
     static std::atomic<unsigned long long> attr_devices{0};
-    int dev = 0;
-    e = hipGetDevice(&dev);
+    e = raise_lds_limit((const void *)blocked_pack_kernel, kPackLds, attr_devices);
     if (e != hipSuccess) return e;
-    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
-    if (!bit || !(attr_devices.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void *)blocked_pack_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)kPackLds);
-        if (e != hipSuccess) return e;
-        attr_devices.fetch_or(bit, std::memory_order_release);
-    }
     const int64_t groups = blocked_chunks(batch) * nparts;
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
     blocked_pack_kernel<<<(unsigned)groups, kPackThreads, kPackLds, s>>>(n, batch, nparts, yb, pcnt, row_ptr, out_col,

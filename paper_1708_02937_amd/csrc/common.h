@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace sdnn {
 
 // A weight entry packed for one 64-bit load: the other end of the edge and its fp32 value.
@@ -41,6 +43,18 @@ __device__ __forceinline__ float activate(double z, double ymax) {
     if (z < 0.0) z = 0.0;
     if (z > ymax) z = ymax;
     return (float)z;
+}
+
+// Raises a kernel's dynamic LDS limit, once per device (bit d of `done`; devices beyond 63 on every call).
+inline hipError_t raise_lds_limit(const void *kernel, size_t bytes, std::atomic<unsigned long long> &done) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+    if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
 }
 
 // ---------------------------------------------------------------- launchers (defined in the .hip files)
@@ -101,7 +115,7 @@ struct ResidentLayer {
     const uint16_t *order;  // neuron of every (slice, lane), 0xffff past the end
     const float *bias;
 };
-bool resident_planned(int64_t n, int64_t nnz);     // set-up builds a layer's interleaved lists
+bool resident_planned(int64_t n);     // set-up builds a layer's interleaved lists
 size_t resident_bytes(int64_t n, int64_t nnz);
 ResidentLayer resident_layer(void *mem, int64_t n, const float *bias);
 // total (device) receives the number of blocks
@@ -111,6 +125,9 @@ hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *
 // only when above 1).  y_out may equal y_in when parts is 1.
 hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t n, int64_t batch, int v, int parts,
                                 double ymax, int pattern, const float *y_in, float *y_out, hipStream_t s);
+// Z = Y (+).(x) W over a semiring (batch-major, no bias or activation; z may equal y when parts is 1).
+hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, int64_t n, int64_t batch, int v, int parts,
+                                    const float *y, float *z, hipStream_t s);
 
 // gemm.hip
 hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s);
@@ -225,7 +242,8 @@ hipError_t launch_semiring_mxm(int semiring, int64_t n, int64_t batch, int64_t l
                                const float *yt, float *zt, hipStream_t s);
 // Z (batch x n, row-major) = Y (+).(x) W for CSR rows Y, row by row from W's packed fan-out rows (w_ptr = W's
 // row pointers, w = (column, weight) pairs), without densifying Y (extents and columns checked, flagged in err).
-hipError_t launch_semiring_rows(int semiring, int64_t n, int64_t batch, const int64_t *row_ptr, const int32_t *col,
-                                const float *val, const int64_t *w_ptr, const Edge *w, float *z, uint32_t *err,
+// nnz: W's entries.
+hipError_t launch_semiring_rows(int semiring, int64_t n, int64_t batch, int64_t nnz, const int64_t *row_ptr,
+                                const int32_t *col, const float *val, const int64_t *w_ptr, const Edge *w, float *z, uint32_t *err,
                                 hipStream_t s);
 }  // namespace sdnn

@@ -3,8 +3,8 @@
 //
 // A workgroup (16 wave64s, one per CU) owns V samples (4, 2 or 1) and keeps all n activations of them in LDS as
 // rows of V floats, one row per neuron; a lane owns one output neuron, walks its fan-in list in ascending input
-// order, reads the input's row (one LDS read of V floats) and adds the V exact products to its fp64 sums.  The
-// bias, h and the rounding follow, and the outputs form the next layer's rows in a second LDS buffer, so a whole
+// order, reads the input's row (one LDS read of V floats) and adds the V exact products to its fp64 sums (or folds
+// them over another semiring of Sec. II, one layer without bias and activation).  The bias, h and the rounding follow, and the outputs form the next layer's rows in a second LDS buffer, so a whole
 // range of layers is one launch: the batch is read once, batch-major, and written once, and nothing else of it
 // touches memory.
 //
@@ -23,7 +23,6 @@
 // entry).  Lists are padded to their slice's longest with entries of weight 0 at input n, a row that holds
 // zeros, which leave a sum as it is.
 #include <algorithm>
-#include <atomic>
 
 #include "common.h"
 
@@ -41,8 +40,8 @@ constexpr int kMaxLds = 160 * 1024;
 
 // ------------------------------------------------------------------------------------------ set-up
 
-// One workgroup per run: its neurons by list length (longest first, ties by index) into order[], and the blocks
-// of every slice.
+// One workgroup per run: its neurons by list length (longest first, ties by index) into order[], and the block
+// counts of every slice (low half: of its longest list; high half: whole blocks of its shortest).
 __global__ __launch_bounds__(kRunLen) void resident_order_kernel(int64_t n, const int64_t *__restrict__ fan_ptr,
                                                                  uint16_t *__restrict__ order,
                                                                  uint2 *__restrict__ slices) {
@@ -66,8 +65,10 @@ __global__ __launch_bounds__(kRunLen) void resident_order_kernel(int64_t n, cons
         }
     const uint32_t mine = key[t];
     order[j] = mine == 0xffffffffu ? (uint16_t)0xffffu : (uint16_t)((int64_t)blockIdx.x * kRunLen + (mine & 1023u));
-    if ((t & 63) == 0)  // the slice's first list is its longest
-        slices[j / 64].y = mine == 0xffffffffu ? 0u : (kResidentMaxN - (mine >> 10) + 3u) / 4u;
+    // the slice's first list is its longest, its last the shortest: blocks, and those no list is padded in
+    const uint32_t l = mine == 0xffffffffu ? 0u : kResidentMaxN - (mine >> 10);
+    const uint32_t shortest = __shfl(l, 63);
+    if ((t & 63) == 0) slices[j / 64].y = (l + 3u) / 4u | shortest / 4u << 16;
 }
 
 // First block of every slice (exclusive sums of the block counts) and their total: one workgroup.
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(64) void resident_scan_kernel(int nslices, uint2 *_
     uint32_t run = 0;
     for (int base = 0; base < nslices; base += 64) {
         const int s = base + (int)threadIdx.x;
-        const uint32_t c = s < nslices ? slices[s].y : 0u;
+        const uint32_t c = s < nslices ? slices[s].y & 0xffffu : 0u;
         uint32_t incl = c;
         for (int d = 1; d < 64; d <<= 1) {
             const uint32_t v = __shfl_up(incl, d);
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(64) void resident_fill_kernel(int64_t n, const int6
         e0 = fan_ptr[j];
         len = (uint32_t)(fan_ptr[j + 1] - e0);
     }
-    for (uint32_t b = blockIdx.y; b < sl.y; b += gridDim.y) {
+    for (uint32_t b = blockIdx.y; b < (sl.y & 0xffffu); b += gridDim.y) {
         uint32_t idx[4];
         float w[4];
 #pragma unroll
@@ -166,11 +167,63 @@ __device__ __forceinline__ typename RowOf<V>::T pack(const float (&y)[V]) {
         return make_float4(y[0], y[1], y[2], y[3]);
 }
 
+// What a lane does with an entry: acc (+)= y (x) w, starting from the 0-element, which is also what the padding's
+// input row holds.  The forward's products are exact and summed in fp64.  The semirings that only select or add
+// once work in fp32: rounding is monotonic, so the largest rounded sum is the rounded largest sum, and a sum of two
+// fp32 values rounded through fp64 is the fp32 sum.  A selection keeps a NaN only until the next entry, so there
+// padded entries are skipped (kGuard) rather than folded in.
+template <bool kPattern_>
+struct Forward {
+    using Acc = double;
+    static constexpr bool kLayer = true, kPattern = kPattern_, kGuard = false;
+    static __device__ float zero() { return 0.0f; }
+    static __device__ void fold(double &a, float y, float w) { a = __builtin_fma((double)y, (double)w, a); }
+};
+struct PlusTimes {
+    using Acc = double;
+    static constexpr bool kLayer = false, kPattern = false, kGuard = false;
+    static __device__ float zero() { return 0.0f; }
+    static __device__ void fold(double &a, float y, float w) { a = __builtin_fma((double)y, (double)w, a); }
+};
+struct MaxPlus {
+    using Acc = float;
+    static constexpr bool kLayer = false, kPattern = false, kGuard = true;
+    static __device__ float zero() { return -__builtin_huge_valf(); }
+    static __device__ void fold(float &a, float y, float w) {
+        const float p = y + w;
+        a = a > p ? a : p;
+    }
+};
+struct MaxMin {
+    using Acc = float;
+    static constexpr bool kLayer = false, kPattern = false, kGuard = true;
+    static __device__ float zero() { return -__builtin_huge_valf(); }
+    static __device__ void fold(float &a, float y, float w) {
+        const float p = y < w ? y : w;
+        a = a > p ? a : p;
+    }
+};
+struct MinMax {
+    using Acc = float;
+    static constexpr bool kLayer = false, kPattern = false, kGuard = true;
+    static __device__ float zero() { return __builtin_huge_valf(); }
+    static __device__ void fold(float &a, float y, float w) {
+        const float p = y > w ? y : w;
+        a = a < p ? a : p;
+    }
+};
+struct XorAnd {  // GF(2): a value counts as 1 when it is nonzero
+    using Acc = uint32_t;
+    static constexpr bool kLayer = false, kPattern = false, kGuard = false;
+    static __device__ float zero() { return 0.0f; }
+    static __device__ void fold(uint32_t &a, float y, float w) { a ^= (uint32_t)(y != 0.0f) & (uint32_t)(w != 0.0f); }
+};
+
 constexpr int kAhead = 3;  // blocks in flight per wave
 
 // A slice a wave is about to walk: its first blocks are already on their way.
 struct Slice {
-    uint32_t first, count;
+    uint32_t first, count, whole;
     uint32_t j;
     uint2 i[kAhead];
     float4 w[kAhead];
@@ -178,7 +231,7 @@ struct Slice {
 
 // grid: (sample groups, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
 // part (a single layer then) every part's workgroup reads all input rows and writes its own neurons.
-template <int V, bool kPattern>
+template <int V, class Op>
 __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs args, int layers, int n, int64_t batch,
                                                                   int nslices, int runs, double ymax,
                                                                   const float *__restrict__ y_in,
@@ -204,13 +257,14 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
     };
     auto fetch = [&](const ResidentLayer &l, int run, Slice &s) {
         const int q = slice_of(run);
-        s.count = 0;
+        s.count = s.whole = 0;
         s.first = 0;
         s.j = 0xffffu;
         if (q < nslices) {
             const uint2 d = l.slices[q];
             s.first = __builtin_amdgcn_readfirstlane(d.x);
-            s.count = __builtin_amdgcn_readfirstlane(d.y);
+            s.count = __builtin_amdgcn_readfirstlane(d.y & 0xffffu);
+            s.whole = __builtin_amdgcn_readfirstlane(d.y >> 16);
             s.j = l.order[q * 64 + lane];
             if (s.count > 0) {
 #pragma unroll
@@ -225,7 +279,7 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
     for (int i = tid; i <= n; i += kRThreads) {
         float y[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) y[v] = (v < rows && i < n) ? y_in[(r0 + v) * n + i] : 0.0f;
+        for (int v = 0; v < V; ++v) y[v] = (v < rows && i < n) ? y_in[(r0 + v) * n + i] : Op::zero();
         src[i] = pack<V>(y);
         // both buffers end in the zero row (with several parts, dst holds one part's outputs and is never read as
         // an input)
@@ -244,15 +298,16 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
                 fetch(args.layer[k + 1], run0, next);
             const char *blocks = l.blocks;
             const bool real = cur.j != 0xffffu;
-            const float bj = l.bias[real ? cur.j : 0];
-            double acc[V];
+            float bj = 0.0f;
+            if constexpr (Op::kLayer) bj = l.bias[real ? cur.j : 0];
+            typename Op::Acc acc[V];
             uint32_t hit[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                acc[v] = 0.0;
+                acc[v] = (typename Op::Acc)Op::zero();
                 hit[v] = 0u;
             }
-            auto block = [&](const uint2 &i, const float4 &w) {
+            auto block = [&](const uint2 &i, const float4 &w, bool whole) {
                 const uint32_t at[4] = {i.x & 0xffffu, i.x >> 16, i.y & 0xffffu, i.y >> 16};
                 const float wv[4] = {w.x, w.y, w.z, w.w};
                 Row r[4];
@@ -262,11 +317,12 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
                 for (int u = 0; u < 4; ++u) {
                     float y[V];
                     unpack<V>(r[u], y);
-                    const double wd = (double)wv[u];
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
-                        acc[v] = __builtin_fma((double)y[v], wd, acc[v]);
-                        if constexpr (kPattern) hit[v] |= __float_as_uint(y[v]);
+                        typename Op::Acc a = acc[v];
+                        Op::fold(a, y[v], wv[u]);
+                        acc[v] = (!Op::kGuard || whole || at[u] != (uint32_t)n) ? a : acc[v];
+                        if constexpr (Op::kPattern) hit[v] |= __float_as_uint(y[v]);
                     }
                 }
             };
@@ -275,23 +331,38 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
             const uint32_t count = __builtin_amdgcn_readfirstlane(cur.count);
             const uint32_t first = __builtin_amdgcn_readfirstlane(cur.first);
             const uint32_t last = first + count - 1;
+            const uint32_t whole = Op::kGuard ? __builtin_amdgcn_readfirstlane(cur.whole) : count;
             uint32_t b = 0;
-            for (; b + kAhead <= count; b += kAhead) {
+            // whole blocks, kAhead at a time
+            for (; b + kAhead <= whole; b += kAhead) {
 #pragma unroll
                 for (int q = 0; q < kAhead; ++q) {
-                    block(cur.i[q], cur.w[q]);
+                    block(cur.i[q], cur.w[q], true);
                     load(blocks, min(first + b + kAhead + q, last), cur.i[q], cur.w[q]);
                     __builtin_amdgcn_sched_barrier(0);  // the load stays here, a block ahead of the next set's
                 }
             }
+            if constexpr (Op::kGuard) {
+                for (; b + kAhead <= count; b += kAhead) {
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) {
+                        block(cur.i[q], cur.w[q], false);
+                        load(blocks, min(first + b + kAhead + q, last), cur.i[q], cur.w[q]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
 #pragma unroll
             for (int q = 0; q + 1 < kAhead; ++q)
-                if (b + q < count) block(cur.i[q], cur.w[q]);
+                if (b + q < count) block(cur.i[q], cur.w[q], false);
             if (real) {
                 float out[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    out[v] = (kPattern && (hit[v] & 0x7fffffffu) == 0u) ? 0.0f : activate(acc[v] + (double)bj, ymax);
+                    if constexpr (Op::kLayer)
+                        out[v] = (Op::kPattern && (hit[v] & 0x7fffffffu) == 0u) ? 0.0f : activate(acc[v] + (double)bj, ymax);
+                    else
+                        out[v] = (float)acc[v];
                 dst[(int)cur.j - j0] = pack<V>(out);
             }
         }
@@ -326,7 +397,7 @@ size_t resident_bytes(int64_t n, int64_t nnz) {
     return (size_t)(resident_slices(n) * (64 * 2 + 8) + 256 + blocks * kBlockBytes);
 }
 
-bool resident_planned(int64_t n, int64_t nnz) { return n <= kResidentMaxN && !spmm_wants_tiles(n, nnz); }
+bool resident_planned(int64_t n) { return n <= kResidentMaxN; }
 
 ResidentLayer resident_layer(void *mem, int64_t n, const float *bias) {
     ResidentLayer l;
@@ -358,7 +429,7 @@ hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *
 
 namespace {
 
-template <int V, bool kPattern>
+template <int V, class Op>
 hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t batch, int parts, double ymax,
                     const float *y_in, float *y_out, hipStream_t s) {
     const int64_t runs = (n + kRunLen - 1) / kRunLen;
@@ -366,23 +437,25 @@ hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t bat
     parts = (int)((runs + per - 1) / per);
     const size_t lds = lds_bytes(n, V, parts > 1 ? (int64_t)per * kRunLen : n + 1);
     if (lds > (size_t)kMaxLds) return hipErrorInvalidValue;
-    // more LDS than the default dynamic limit: raised once per device (bit d; devices beyond 63 on every call)
     static std::atomic<unsigned long long> attr_devices{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = raise_lds_limit((const void *)spmm_resident_kernel<V, Op>, kMaxLds, attr_devices);
     if (e != hipSuccess) return e;
-    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
-    if (!bit || !(attr_devices.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void *)spmm_resident_kernel<V, kPattern>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
-        if (e != hipSuccess) return e;
-        attr_devices.fetch_or(bit, std::memory_order_release);
-    }
     const int64_t groups = (batch + V - 1) / V;
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-    spmm_resident_kernel<V, kPattern><<<dim3((unsigned)groups, (unsigned)parts), kRThreads, lds, s>>>(
+    spmm_resident_kernel<V, Op><<<dim3((unsigned)groups, (unsigned)parts), kRThreads, lds, s>>>(
         args, layers, (int)n, batch, (int)((n + 63) / 64), per, ymax, y_in, y_out);
     return hipGetLastError();
+}
+
+template <class Op>
+hipError_t launch_op(const ResidentArgs &args, int layers, int64_t n, int64_t batch, int v, int parts, double ymax,
+                     const float *y_in, float *y_out, hipStream_t s) {
+    switch (v) {
+        case 1: return launch_v<1, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 2: return launch_v<2, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 4: return launch_v<4, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -393,13 +466,21 @@ hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t 
         return hipErrorInvalidValue;
     ResidentArgs args;
     for (int k = 0; k < layers; ++k) args.layer[k] = layer[k];
-    switch (v * 2 + (pattern ? 1 : 0)) {
-        case 2: return launch_v<1, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 3: return launch_v<1, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 4: return launch_v<2, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 5: return launch_v<2, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 8: return launch_v<4, false>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 9: return launch_v<4, true>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+    return pattern ? launch_op<Forward<true>>(args, layers, n, batch, v, parts, ymax, y_in, y_out, s)
+                   : launch_op<Forward<false>>(args, layers, n, batch, v, parts, ymax, y_in, y_out, s);
+}
+
+hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, int64_t n, int64_t batch, int v, int parts,
+                                    const float *y, float *z, hipStream_t s) {
+    if (n > kResidentMaxN) return hipErrorInvalidValue;
+    ResidentArgs args;
+    args.layer[0] = layer;
+    switch (semiring) {
+        case kSemiringPlusTimes: return launch_op<PlusTimes>(args, 1, n, batch, v, parts, 0.0, y, z, s);
+        case kSemiringMaxPlus: return launch_op<MaxPlus>(args, 1, n, batch, v, parts, 0.0, y, z, s);
+        case kSemiringMaxMin: return launch_op<MaxMin>(args, 1, n, batch, v, parts, 0.0, y, z, s);
+        case kSemiringMinMax: return launch_op<MinMax>(args, 1, n, batch, v, parts, 0.0, y, z, s);
+        case kSemiringXorAnd: return launch_op<XorAnd>(args, 1, n, batch, v, parts, 0.0, y, z, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -7,6 +7,7 @@
 // ascending input order), broadcasting each entry with readlane.  Values are carried in fp64 and rounded
 // once to fp32: +.x multiplies exactly and sums in fp64 as the forward pass does; max.+ adds in fp64 and
 // max.min, min.max and xor.and only select or compare, so those four are exact.
+#include <atomic>
 #include <type_traits>
 
 #include "common.h"
@@ -123,81 +124,156 @@ __global__ __launch_bounds__(256) void semiring_gather_kernel(int64_t n, int64_t
 }
 
 // Row-wise product on CSR input (the SpGEMM skeleton of the forward pass, Sec. II.D computed row by row):
-// one workgroup per sample keeps a window of kSrWin output columns in LDS, initialised to the 0-element;
-// each wave takes one stored entry (i, y) of the sample at a time and its lanes walk the window's part of
-// W_k's fan-out row i (rows are sorted by column, so the part is found by binary search), folding y (x) w
-// into the column's slot with an LDS atomic ((+) is an fp64 add, max, min or, for GF(2), an exclusive or).
+// a workgroup takes one sample and one window of at most kSrWin output columns, kept in LDS and initialised to
+// the 0-element.  A wave takes 64 stored entries (i, y) of the sample at a time: its lanes look up their entry's
+// fan-out row of W_k (a row is sorted by column: the window's part of it by binary search) and leave (first,
+// count, y) in LDS; then groups of `width` lanes walk one row each, kSrAhead rows of every group in flight, and
+// fold y (x) w into the column's slot with an LDS atomic ((+) is an fp64 add, max, min or, for GF(2), an
+// exclusive or).  `width` is the power of two at the layer's mean row part, so short rows leave no lane idle.
+// What bounds it: the chain of dependent loads per 64 entries (column, row extent, entries), which the waves of
+// a CU overlap, then the LDS atomics.  One row per wave at a time (its extent and entries each a round trip) took
+// 555 us at n 16384, 32 entries per row, 1024 samples of 10%.
 // Unstored entries are the 0-element, which changes nothing, so only stored ones are visited; the window
 // is written to Z's row (batch-major) as fp32.  +.x sums exact products in fp64 in the order the atomics
 // land and rounds once; the other semirings only select, compare or count, so they are exact.  Row extents
 // and columns are checked as in the forward pass (flagged, offending rows or entries skipped).
 constexpr int kSrWin = 16384;
-constexpr int kSrThreads = 512;
+constexpr int kSrThreads = 1024;
+constexpr int kSrAhead = 4;
+
+struct __align__(16) SrRow {
+    uint32_t first;  // fewer than 2^31 entries
+    uint32_t count;
+    float y;
+    uint32_t pad;
+};
+
+// first entry of the sorted part [a, e) of a row whose column is at least c
+__device__ __forceinline__ int64_t first_at(const Edge *w, int64_t a, int64_t e, int64_t c) {
+    while (a < e) {
+        const int64_t m = (a + e) >> 1;
+        if (w[m].idx < c) a = m + 1;
+        else e = m;
+    }
+    return a;
+}
 
 template <class SR>
-__global__ __launch_bounds__(kSrThreads) void semiring_rows_kernel(int64_t n, int64_t batch,
+__global__ __launch_bounds__(kSrThreads) void semiring_rows_kernel(int64_t n, int64_t batch, int64_t r0, int win,
+                                                                   int width_log,
                                                                    const int64_t *__restrict__ row_ptr,
                                                                    const int32_t *__restrict__ col,
                                                                    const float *__restrict__ val,
                                                                    const int64_t *__restrict__ w_ptr,
                                                                    const Edge *__restrict__ w, float *__restrict__ z,
                                                                    uint32_t *err) {
-    __shared__ double acc[kSrWin];
-    const int64_t r = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kW = kSrThreads / 64;
+    extern __shared__ __align__(16) char sr_lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    SrRow *rows = reinterpret_cast<SrRow *>(sr_lds) + wave * 64;  // the wave's own
+    double *acc = reinterpret_cast<double *>(sr_lds + waves * 64 * sizeof(SrRow));
+    const int64_t r = r0 + blockIdx.x;
+    const int64_t w0 = (int64_t)blockIdx.y * win;
+    const int wn = (int)(n - w0 < win ? n - w0 : win);
     const int64_t nnz = (col && val) ? row_ptr[batch] : 0;
-    int64_t b = row_ptr[r], len = row_ptr[r + 1] - b;
+    const int64_t b = row_ptr[r];
+    int64_t len = row_ptr[r + 1] - b;
     if (b < 0 || len < 0 || len > n || b + len > nnz) {
         if (threadIdx.x == 0) atomicOr(err, 1u);
         len = 0;
     }
-    for (int64_t w0 = 0; w0 < n; w0 += kSrWin) {
-        const int64_t wn = n - w0 < kSrWin ? n - w0 : kSrWin;
-        for (int64_t c = threadIdx.x; c < wn; c += kSrThreads) slot_init<SR>(&acc[c]);
-        __syncthreads();
-        for (int64_t t = wave; t < len; t += kW) {
-            const int32_t i = col[b + t];
+    for (int c = threadIdx.x; c < wn; c += blockDim.x) slot_init<SR>(&acc[c]);
+    __syncthreads();
+    const int width = 1 << width_log, sub = lane & (width - 1), group = lane >> width_log;
+    const int groups = 64 >> width_log;
+    for (int64_t t0 = (int64_t)wave * 64; t0 < len; t0 += (int64_t)waves * 64) {
+        const int m = (int)(len - t0 < 64 ? len - t0 : 64);
+        SrRow row{0, 0, 0.0f, 0};
+        if (lane < m) {
+            const int32_t i = col[b + t0 + lane];
+            row.y = val[b + t0 + lane];
             if (i < 0 || i >= n) {
-                if (lane == 0 && w0 == 0) atomicOr(err, 1u);
-                continue;
-            }
-            const double y = (double)val[b + t];
-            int64_t lo = w_ptr[i], hi = w_ptr[(int64_t)i + 1];
-            if (w0 > 0 || wn < n) {  // the window's part of the sorted row: [first col >= w0, first col >= w0 + wn)
-                int64_t a = lo, e = hi;
-                while (a < e) {
-                    const int64_t m = (a + e) >> 1;
-                    if (w[m].idx < w0) a = m + 1;
-                    else e = m;
+                if (w0 == 0) atomicOr(err, 1u);
+            } else {
+                int64_t lo = w_ptr[i], hi = w_ptr[(int64_t)i + 1];
+                if (wn < n) {
+                    lo = first_at(w, lo, hi, w0);
+                    hi = first_at(w, lo, hi, w0 + wn);
                 }
-                int64_t a2 = a, e2 = hi;
-                while (a2 < e2) {
-                    const int64_t m = (a2 + e2) >> 1;
-                    if (w[m].idx < w0 + wn) a2 = m + 1;
-                    else e2 = m;
-                }
-                lo = a;
-                hi = a2;
-            }
-            for (int64_t q = lo + lane; q < hi; q += 64) {
-                const Edge ed = w[q];
-                SR::fold(&acc[ed.idx - w0], SR::mul(y, (double)ed.w));
+                row.first = (uint32_t)lo;
+                row.count = (uint32_t)(hi - lo);
             }
         }
-        __syncthreads();
-        float *zr = z + r * n + w0;
-        for (int64_t c = threadIdx.x; c < wn; c += kSrThreads) zr[c] = (float)slot_value<SR>(&acc[c]);
-        __syncthreads();
+        rows[lane] = row;
+        // LDS writes and reads of one wave, in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int e0 = 0; e0 < m; e0 += groups * kSrAhead) {
+            Edge ed[kSrAhead];
+            SrRow rw[kSrAhead];
+#pragma unroll
+            for (int u = 0; u < kSrAhead; ++u) {
+                const int e = e0 + u * groups + group;
+                rw[u] = rows[e < 64 ? e : 63];
+                if (e >= 64) rw[u].count = 0;
+                ed[u] = Edge{0, 0.0f};
+                if ((uint32_t)sub < rw[u].count) ed[u] = w[rw[u].first + (uint32_t)sub];
+            }
+#pragma unroll
+            for (int u = 0; u < kSrAhead; ++u)
+                if ((uint32_t)sub < rw[u].count) SR::fold(&acc[ed[u].idx - w0], SR::mul((double)rw[u].y, (double)ed[u].w));
+            // the rest of the rows longer than a group
+#pragma unroll
+            for (int u = 0; u < kSrAhead; ++u) {
+                for (uint32_t q = (uint32_t)(sub + width); q < rw[u].count; q += (uint32_t)(width * kSrAhead)) {
+                    Edge er[kSrAhead];
+#pragma unroll
+                    for (int x = 0; x < kSrAhead; ++x) {
+                        const uint32_t qx = q + (uint32_t)(x * width);
+                        er[x] = w[rw[u].first + (qx < rw[u].count ? qx : q)];
+                    }
+#pragma unroll
+                    for (int x = 0; x < kSrAhead; ++x)
+                        if (q + (uint32_t)(x * width) < rw[u].count)
+                            SR::fold(&acc[er[x].idx - w0], SR::mul((double)rw[u].y, (double)er[x].w));
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
+    __syncthreads();
+    float *zr = z + r * n + w0;
+    for (int c = threadIdx.x; c < wn; c += blockDim.x) zr[c] = (float)slot_value<SR>(&acc[c]);
 }
 
 template <class SR>
-hipError_t launch_sr_rows(int64_t n, int64_t batch, const int64_t *row_ptr, const int32_t *col, const float *val,
-                          const int64_t *w_ptr, const Edge *w, float *z, uint32_t *err, hipStream_t s) {
+hipError_t launch_sr_rows(int64_t n, int64_t batch, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
+                          const float *val, const int64_t *w_ptr, const Edge *w, float *z, uint32_t *err, hipStream_t s) {
     if (batch > 0x7fffffffLL) return hipErrorInvalidValue;
-    semiring_rows_kernel<SR><<<(unsigned)batch, kSrThreads, 0, s>>>(n, batch, row_ptr, col, val, w_ptr, w, z, err);
-    return hipGetLastError();
+    // equal windows; lanes per row from the mean row part of a window
+    const int64_t nwin = (n + kSrWin - 1) / kSrWin;
+    if (nwin > 65535) return hipErrorInvalidValue;
+    const int64_t win = (n + nwin - 1) / nwin;
+    int width_log = 2;
+    while (width_log < 6 && ((int64_t)1 << width_log) * n * nwin < nnz) ++width_log;
+    // 16 waves per CU where a window takes most of its LDS, else 8 per workgroup and several workgroups
+    const int threads = win > kSrWin / 2 ? kSrThreads : kSrThreads / 2;
+    const size_t lds = (size_t)win * sizeof(double) + (size_t)threads * sizeof(SrRow);
+    static std::atomic<unsigned long long> attr_devices{0};
+    hipError_t e = raise_lds_limit((const void *)semiring_rows_kernel<SR>,
+                                   kSrWin * sizeof(double) + kSrThreads * sizeof(SrRow), attr_devices);
+    if (e != hipSuccess) return e;
+    constexpr int64_t kSeg = 1ll << 21;  // samples per launch: fewer than 2^32 work-items
+    for (int64_t r0 = 0; r0 < batch; r0 += kSeg) {
+        const unsigned nb = (unsigned)(batch - r0 < kSeg ? batch - r0 : kSeg);
+        semiring_rows_kernel<SR><<<dim3(nb, (unsigned)nwin), threads, lds, s>>>(n, batch, r0, (int)win, width_log, row_ptr,
+                                                                               col, val, w_ptr, w, z, err);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <class SR>
@@ -247,16 +323,16 @@ hipError_t launch_semiring_mxm(int semiring, int64_t n, int64_t batch, int64_t l
     }
 }
 
-hipError_t launch_semiring_rows(int semiring, int64_t n, int64_t batch, const int64_t *row_ptr, const int32_t *col,
-                                const float *val, const int64_t *w_ptr, const Edge *w, float *z, uint32_t *err,
-                                hipStream_t s) {
+hipError_t launch_semiring_rows(int semiring, int64_t n, int64_t batch, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
+                                const float *val, const int64_t *w_ptr, const Edge *w, float *z,
+                                uint32_t *err, hipStream_t s) {
     if (n == 0 || batch == 0) return hipSuccess;
     switch (semiring) {
-        case kSemiringPlusTimes: return launch_sr_rows<PlusTimes>(n, batch, row_ptr, col, val, w_ptr, w, z, err, s);
-        case kSemiringMaxPlus: return launch_sr_rows<MaxPlus>(n, batch, row_ptr, col, val, w_ptr, w, z, err, s);
-        case kSemiringMaxMin: return launch_sr_rows<MaxMin>(n, batch, row_ptr, col, val, w_ptr, w, z, err, s);
-        case kSemiringMinMax: return launch_sr_rows<MinMax>(n, batch, row_ptr, col, val, w_ptr, w, z, err, s);
-        case kSemiringXorAnd: return launch_sr_rows<XorAnd>(n, batch, row_ptr, col, val, w_ptr, w, z, err, s);
+        case kSemiringPlusTimes: return launch_sr_rows<PlusTimes>(n, batch, nnz, row_ptr, col, val, w_ptr, w, z, err, s);
+        case kSemiringMaxPlus: return launch_sr_rows<MaxPlus>(n, batch, nnz, row_ptr, col, val, w_ptr, w, z, err, s);
+        case kSemiringMaxMin: return launch_sr_rows<MaxMin>(n, batch, nnz, row_ptr, col, val, w_ptr, w, z, err, s);
+        case kSemiringMinMax: return launch_sr_rows<MinMax>(n, batch, nnz, row_ptr, col, val, w_ptr, w, z, err, s);
+        case kSemiringXorAnd: return launch_sr_rows<XorAnd>(n, batch, nnz, row_ptr, col, val, w_ptr, w, z, err, s);
         default: return hipErrorInvalidValue;
     }
 }
