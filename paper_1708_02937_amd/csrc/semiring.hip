@@ -181,14 +181,13 @@ __global__ __launch_bounds__(kSrThreads) void semiring_rows_kernel(int64_t n, in
         if (threadIdx.x == 0) atomicOr(err, 1u);
         len = 0;
     }
-    for (int c = threadIdx.x; c < wn; c += blockDim.x) slot_init<SR>(&acc[c]);
-    __syncthreads();
-    const int width = 1 << width_log, sub = lane & (width - 1), group = lane >> width_log;
-    const int groups = 64 >> width_log;
-    for (int64_t t0 = (int64_t)wave * 64; t0 < len; t0 += (int64_t)waves * 64) {
-        const int m = (int)(len - t0 < 64 ? len - t0 : 64);
+    // every wave takes an equal share of the entries, 64 at a time; an entry's column and row extent are loaded
+    // while the 64 before it are folded in (the first while the window is initialised)
+    const int64_t share = (len + waves - 1) / waves;
+    const int64_t t_end = (int64_t)(wave + 1) * share < len ? (int64_t)(wave + 1) * share : len;
+    auto lookup = [&](int64_t t0) {
         SrRow row{0, 0, 0.0f, 0};
-        if (lane < m) {
+        if (t0 + lane < t_end) {
             const int32_t i = col[b + t0 + lane];
             row.y = val[b + t0 + lane];
             if (i < 0 || i >= n) {
@@ -203,6 +202,17 @@ __global__ __launch_bounds__(kSrThreads) void semiring_rows_kernel(int64_t n, in
                 row.count = (uint32_t)(hi - lo);
             }
         }
+        return row;
+    };
+    SrRow next = lookup((int64_t)wave * share);
+    for (int c = threadIdx.x; c < wn; c += blockDim.x) slot_init<SR>(&acc[c]);
+    __syncthreads();
+    const int width = 1 << width_log, sub = lane & (width - 1), group = lane >> width_log;
+    const int groups = 64 >> width_log;
+    for (int64_t t0 = (int64_t)wave * share; t0 < t_end; t0 += 64) {
+        const int m = (int)(t_end - t0 < 64 ? t_end - t0 : 64);
+        const SrRow row = next;
+        next = lookup(t0 + 64);
         rows[lane] = row;
         // LDS writes and reads of one wave, in order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

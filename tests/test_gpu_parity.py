@@ -1111,3 +1111,25 @@ def test_arena_is_the_only_device_memory(sd):
             parity.compare(p, dense_to_csr(net.forward_dense(y).cpu().numpy()))  # still usable
         net.free()
         del ws
+
+
+@pytest.mark.parametrize("n,batch,rows", [(5000, 260, 3), (20000, 300, 1), (33000, 257, 2)])
+@pytest.mark.parametrize("bad", ["first", "middle", "last", "negative"])
+def test_blocked_densify_checks_every_column(sd, n, batch, rows, bad):
+    """An out-of-range column anywhere in a row of a batch that goes straight to the sample-blocked layout is
+    reported (the parts of the neurons share the check), whatever the batch (few chunks: many parts), and the net
+    stays usable."""
+    p = tiny_random(n, n, 1, batch, w_density=20 / n, y_density=0.2, bias_lo=0.0, bias_hi=0.2)
+    net = sd.net_from_problem(p)
+    rp, c, v = p.y0_csr
+    for r in range(0, batch, max(1, batch // rows)):
+        at = {"first": rp[r], "negative": rp[r], "middle": (rp[r] + rp[r + 1]) // 2, "last": rp[r + 1] - 1}[bad]
+        wrong = c.copy()
+        wrong[at] = -1 if bad == "negative" else n
+        _say("blocked densify check", n, batch, bad, r)
+        with pytest.raises(sd.SdnnError) as e:
+            net.forward_csr(rp, wrong, v)
+        assert e.value.name == "SDNN_ERR_INVALID_INDEX"
+    got = [x.cpu().numpy() for x in net.forward_csr(rp, c, v)]
+    net.free()
+    parity.compare(p, tuple(got))
