@@ -253,10 +253,11 @@ int64_t sdnn_noalloc_scratch_bytes(void);
  * sdnn_workspace_size(net, batch, 1) bytes.  Synchronises the net's stream
  * at the end, to read the nnz, and at the activation-format decisions below.
  * Internally, activations stay as sparse rows (row-wise SpGEMM) until the
- * first layer whose input holds at least batch * n / 8 entries or whose bias
- * is positive on at least a quarter of the neurons (its output is then mostly
- * nonzero); from that layer on they are kept dense and neuron-major inside ws
- * and packed back into CSR after the last layer.  The host tracks an upper
+ * first layer whose input holds at least batch * n / 8 entries (/ 16 on the
+ * sample-blocked layout, / 32 for ranges of up to 8 layers on the LDS-resident
+ * product) or whose bias is positive on at least a quarter of the neurons (its
+ * output is then mostly nonzero); from that layer on they are kept dense inside
+ * ws and packed back into CSR after the last layer.  The host tracks an upper
  * bound of each layer's input size and reads the exact count (one stream
  * synchronisation) only when the bound reaches the threshold, always for the
  * first layer.  The result is the same either way.

@@ -272,6 +272,9 @@ struct sdnn_net_s {
     int32_t *d_int = nullptr;
     unsigned long long *d_stats = nullptr;  // kSpgemmStats counters per layer of a forward call
     int num_cu = 256;
+    // pinned host memory: what the kernels of a CSR call report, and four words the set-up copies back
+    sdnn::HostSlot *host = nullptr;
+    uint32_t *host_words = nullptr;
     char *arena = nullptr;  // caller-owned device memory holding everything above and every layer's copies
     NetPlan plan;
     std::vector<int64_t> caps;  // entry capacity of each layer
@@ -466,6 +469,13 @@ sdnn_status sdnn_net_create(sdnn_net *out, int64_t n, int32_t L, float ymax, con
         return fail(SDNN_ERR_UNSUPPORTED, std::string("built for gfx950, device is ") + prop.gcnArchName);
     sdnn_net net = new (std::nothrow) sdnn_net_s();
     if (!net) return fail(SDNN_ERR_OUT_OF_MEMORY, "host allocation failed");
+    if (const hipError_t e = hipHostMalloc((void **)&net->host, sizeof(sdnn::HostSlot) + 4 * sizeof(uint32_t), hipHostMallocDefault);
+        e != hipSuccess) {
+        delete net;
+        (void)hipGetLastError();
+        return fail(SDNN_ERR_OUT_OF_MEMORY, std::string("pinned host allocation failed: ") + hipGetErrorString(e));
+    }
+    net->host_words = reinterpret_cast<uint32_t *>(net->host + 1);
     net->n = n;
     net->L = L;
     net->ymax = (double)ymax;
@@ -517,10 +527,11 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     SDNN_ON_DEVICE(net);
 
     // 1. validate on the device
-    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, 4 * sizeof(uint32_t), s));
+    // (the flags and the set-up's integers are cleared together: d_int follows the flags in the arena)
+    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, (size_t)((char *)(net->d_int + 4) - (char *)net->d_flags), s));
     SDNN_HIP(sdnn::launch_validate_layer(n, nnz, row_ptr, col_idx, val, bias, net->d_flags, s));
-    uint32_t fl[4] = {0, 0, 0, 0};
-    SDNN_HIP(hipMemcpyAsync(fl, net->d_flags, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    const uint32_t *fl = net->host_words;
+    SDNN_HIP(hipMemcpyAsync(net->host_words, net->d_flags, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     SDNN_HIP(hipStreamSynchronize(s));
     const uint32_t flags = fl[0];
     if (flags & 1u)
@@ -583,24 +594,21 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     SETUP_HIP(sdnn::launch_exclusive_scan_i32_to_i64(n, counts, nl.fan_ptr, tmp, s));
     SETUP_HIP(sdnn::launch_fanin_lists(n, nnz, row_ptr, col_idx, val, nl.fan, sort_scratch, s));
     SETUP_HIP(hipMemsetAsync(nl.fan + nnz, 0, sizeof(Edge), s));
-    SETUP_HIP(hipMemsetAsync(net->d_int, 0, sizeof(int32_t), s));
     SETUP_HIP(sdnn::launch_max_segment(n, row_ptr, net->d_int, s));
-    SETUP_HIP(hipMemcpyAsync(&nl.max_fanout, net->d_int, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     if (nl.w_seg) SETUP_HIP(sdnn::launch_window_seg(n, row_ptr, col_idx, nl.w_seg, s));
-    int32_t region_max = 0;
     if (nl.sched) {
         SETUP_HIP(sdnn::launch_blocked_order(n, nl.fan_ptr, nl.sched, s));
         SETUP_HIP(sdnn::launch_blocked_stage(n, nnz, nl.fan, nl.sched, nl.stage, regions, counts, starts, tmp,
                                              net->d_int + 1, s));
-        SETUP_HIP(hipMemcpyAsync(&region_max, net->d_int + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
     if (nl.tile_mask) SETUP_HIP(sdnn::launch_spmm_tile_mask(n, nl.fan_ptr, nl.fan, nl.tile_mask, s));
     if (nl.slots) SETUP_HIP(sdnn::launch_spmm_slots(n, nl.fan_ptr, nl.fan, nl.slots, s));
-    if (nl.resident) {
-        SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 2, s));
-        SETUP_HIP(hipMemcpyAsync(&nl.resident_blocks, net->d_int + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    }
+    if (nl.resident) SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 2, s));
+    SETUP_HIP(hipMemcpyAsync(net->host_words, net->d_int, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     SETUP_HIP(hipStreamSynchronize(s));
+    nl.max_fanout = (int32_t)net->host_words[0];
+    const int32_t region_max = (int32_t)net->host_words[1];
+    nl.resident_blocks = (int32_t)net->host_words[2];
 #undef SETUP_HIP
     // the product stages each workgroup's lists in LDS when the longest region fits; otherwise it reads the
     // same staged copy entry by entry
@@ -664,10 +672,11 @@ sdnn_status sdnn_forward_dense_noalloc(sdnn_net net, int32_t k0, int32_t k1, int
 
 int64_t sdnn_noalloc_scratch_bytes(void) { return (int64_t)kScratchBytes; }
 
-// Layers [k0, k1) on the LDS-resident product, batch-major in and out (in may equal out unless the plan splits
-// the neurons); buf: two buffers of batch x n floats for the layers between separate launches.
+// Layers [k0, k1) on the LDS-resident product (io.y_in may equal io.y_out unless the plan splits the neurons); buf:
+// two buffers of batch x n floats for the layers between separate launches.
 static sdnn_status run_resident(sdnn_net net, int32_t k0, int32_t k1, int64_t batch, const ResidentPlan &plan,
-                                const float *in, float *out, float *const buf[2]) {
+                                const sdnn::ResidentIo &io, float *const buf[2]) {
+    sdnn::ResidentIo cur = io;
     const int32_t step = plan.fused ? sdnn::kResidentLayers : 1;
     for (int32_t k = k0; k < k1; k += step) {
         sdnn::ResidentLayer rl[sdnn::kResidentLayers];
@@ -676,13 +685,16 @@ static sdnn_status run_resident(sdnn_net net, int32_t k0, int32_t k1, int64_t ba
             const Layer &l = net->layers[(size_t)(k + i)];
             rl[i] = sdnn::resident_layer(l.resident, net->n, l.bias);
         }
-        float *to = k + count >= k1 ? out : buf[((k - k0) / step) & 1];
+        const bool last = k + count >= k1;
+        cur.y_out = last ? io.y_out : buf[((k - k0) / step) & 1];
+        cur.cnt_out = last ? io.cnt_out : nullptr;
         int pr = -1;
         SDNN_HIP(prof_begin(net, k, sdnn::kKernResident, &pr));
         SDNN_HIP(sdnn::launch_spmm_resident(rl, count, net->n, batch, plan.v, plan.parts, net->ymax,
-                                            net->bias_pattern, in, to, net->stream));
+                                            net->bias_pattern, cur, net->stream));
         SDNN_HIP(prof_end(net, pr));
-        in = to;
+        cur = sdnn::ResidentIo();
+        cur.y_in = last ? io.y_out : buf[((k - k0) / step) & 1];
     }
     return SDNN_OK;
 }
@@ -756,8 +768,12 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
     }
     if (arm == SDNN_ARM_SPARSE && (Y_in == Y_out || !overlap(Y_in, Y_out, (size_t)batch * (size_t)n))) {
         ResidentPlan plan;
-        if (plan_resident(net, k0, k1, batch, Y_in != Y_out, false, &plan))
-            return run_resident(net, k0, k1, batch, plan, Y_in, Y_out, buf);
+        if (plan_resident(net, k0, k1, batch, Y_in != Y_out, false, &plan)) {
+            sdnn::ResidentIo io;
+            io.y_in = Y_in;
+            io.y_out = Y_out;
+            return run_resident(net, k0, k1, batch, plan, io, buf);
+        }
     }
     SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
     SDNN_HIP(sdnn::launch_transpose(Y_in, n, buf[0], ld, batch, n, s));  // batch x n -> n x batch
@@ -831,8 +847,16 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
         *out_nnz = 0;
         return SDNN_OK;
     }
-    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, sizeof(uint32_t), s));
-    SDNN_HIP(hipMemsetAsync(net->d_stats, 0, (size_t)(k1 - k0) * sdnn::kSpgemmStats * sizeof(unsigned long long), s));
+    // what the host waits for comes through pinned memory the kernels write to (a copy to pageable memory costs 10 us
+    // more than a kernel's store and the same synchronisation); the first report also clears the flags and counters
+    SDNN_HIP(sdnn::launch_csr_begin(net->d_flags, net->d_stats, (int64_t)(k1 - k0) * sdnn::kSpgemmStats,
+                                    y_row_ptr + batch, net->host, s));
+    const sdnn::HostReport report{net->host, net->d_flags};
+    auto read_count = [&](int32_t k) -> hipError_t {  // the output entries of sparse layer k, into net->host->nnz
+        const unsigned long long *at = net->d_stats + sdnn::kSpgemmStats * (k - k0) + sdnn::kSpgemmStatNnz;
+        const hipError_t e = sdnn::launch_report(reinterpret_cast<const int64_t *>(at), report, s);
+        return e != hipSuccess ? e : hipStreamSynchronize(s);
+    };
 
     // Activation format per layer.  While outputs are sparse they stay as slot rows (row-wise SpGEMM).
     // From the first layer whose input is dense enough, activations are kept dense and neuron-major and
@@ -847,14 +871,20 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
     // untouched columns stay zero, every b_j <= 0 or bias on the pattern only, writes at most (longest
     // fan-out row) entries per input entry) and reads the exact count from the device only when the bound
     // reaches the threshold.
-    const double dense_at = (double)batch * (double)n / (use_blocked(net, k0, k1, batch) ? 16.0 : 8.0);
+    // Where the LDS-resident product takes over it comes at 1/32, for ranges too short to be stopped early at an empty
+    // activation (n 3001, 32 entries per neuron, batch 1000, a 10%-dense input: the SpGEMM takes 118 us, the resident
+    // product about 12 us per layer and reads the sparse rows itself).
+    constexpr int32_t kEmptyCheckLayers = 8;
+    ResidentPlan probe;
+    const double dense_at =
+        (double)batch * (double)n /
+        (use_blocked(net, k0, k1, batch) ? 16.0
+         : k1 - k0 <= kEmptyCheckLayers && plan_resident(net, k0, k1, batch, false, false, &probe) ? 32.0 : 8.0);
     double nnz_hi = (double)batch * (double)n;  // upper bound of the current layer's input entries
     bool exact = false;
     if (nnz_hi >= dense_at) {
-        int64_t in_nnz = 0;
-        SDNN_HIP(hipMemcpyAsync(&in_nnz, y_row_ptr + batch, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         SDNN_HIP(hipStreamSynchronize(s));
-        nnz_hi = (double)in_nnz;
+        nnz_hi = (double)net->host->nnz;
         exact = true;
     }
     int32_t kd = k1;
@@ -864,7 +894,6 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
     // kEmptyCheckLayers such layers follow, the host reads the layer's output count (one synchronisation) and
     // stops at an empty output, which is then Y_{k1} (the deep sparse network dies out this way after its
     // second layer; the rest would cost launches only).
-    constexpr int32_t kEmptyCheckLayers = 8;
     int64_t next_check = 1;
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
@@ -873,10 +902,8 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
             break;
         }
         if (nnz_hi >= dense_at && !exact) {
-            unsigned long long got = 0;
-            SDNN_HIP(hipMemcpyAsync(&got, net->d_stats + sdnn::kSpgemmStats * (k - 1 - k0) + sdnn::kSpgemmStatNnz, sizeof(got), hipMemcpyDeviceToHost, s));
-            SDNN_HIP(hipStreamSynchronize(s));
-            nnz_hi = (double)got;
+            SDNN_HIP(read_count(k - 1));
+            nnz_hi = (double)net->host->nnz;
             exact = true;
         }
         if (nnz_hi >= dense_at) {
@@ -903,18 +930,14 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
             for (int32_t j = k + 1; stays_empty && j < k1; ++j)
                 stays_empty = net->layers[(size_t)j].bias_nonpos || net->bias_pattern;
             if (stays_empty) {
-                unsigned long long got = 0;
-                SDNN_HIP(hipMemcpyAsync(&got, net->d_stats + sdnn::kSpgemmStats * (k - k0) + sdnn::kSpgemmStatNnz,
-                                        sizeof(got), hipMemcpyDeviceToHost, s));
-                SDNN_HIP(hipStreamSynchronize(s));
-                nnz_hi = (double)got;
+                SDNN_HIP(read_count(k));
+                nnz_hi = (double)net->host->nnz;
                 exact = true;
-                if (got == 0) break;  // Y_{k+1} is empty, and so is every later activation
+                if (net->host->nnz == 0) break;  // Y_{k+1} is empty, and so is every later activation
             }
         }
     }
-    int last = 0, outb;  // slot buffer holding Y_{k1}, and the buffer the packed CSR goes to
-    bool packed = false;  // the CSR is already in buffer outb
+    int outb;  // the buffer the packed CSR goes to
     if (kd < k1 && use_blocked(net, kd, k1, batch)) {
         // dense activations in the sample-blocked layout, packed straight into CSR at the end
         const bool from_user = kd == k0;
@@ -941,69 +964,75 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
             dc ^= 1;
         }
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernPack, &pr));
-        SDNN_HIP(sdnn::launch_blocked_to_csr(n, batch, dense[dc], w.pcnt, w.cnt[db ^ 1], out_row_ptr, w.scan_tmp,
+        SDNN_HIP(sdnn::launch_blocked_to_csr(n, batch, dense[dc], w.pcnt, w.cnt[db ^ 1], out_row_ptr, w.scan_tmp, report,
                                              w.col[db ^ 1], w.val[db ^ 1], s));
         SDNN_HIP(prof_end(net, pr));
-        packed = true;
         outb = db ^ 1;
     } else if (kd < k1) {
         const bool from_user = kd == k0;
         const int db = from_user ? 0 : cur;  // the input rows (if any) sit in buffer cur ^ 1
-        // two n x batch fp32 buffers at row pitch ld
+        // two buffers of n x batch floats at row pitch ld
         float *dense[2] = {reinterpret_cast<float *>(w.col[db]), w.val[db]};
         const int64_t ld = sdnn::act_ld(n, batch);
-        // dense[1] is free until the first layer: it stages the rows batch-major when they hold at least a
-        // quarter of batch * n entries (measured on MI355X: 0.34 instead of 0.69 ms for 32M entries into
-        // 16384 x 4096; at 2% density the extra transpose costs more than the scattered stores it saves)
-        float *stage = nnz_hi >= (double)batch * (double)n / 4.0 ? dense[1] : nullptr;
+        ResidentPlan plan;
         int pr = -1;
-        SDNN_HIP(prof_begin(net, -1, sdnn::kKernDensify, &pr));
-        SDNN_HIP(sdnn::launch_densify(n, batch, ld, from_user ? y_row_ptr : nullptr, from_user ? nullptr : w.cnt[cur ^ 1],
-                                      from_user ? y_col : w.col[cur ^ 1], from_user ? y_val : w.val[cur ^ 1],
-                                      dense[0], stage, net->d_flags, s));
-        SDNN_HIP(prof_end(net, pr));
         int dc = 0;
-        for (int32_t k = kd; k < k1; ++k) {
-            const Layer &l = net->layers[(size_t)k];
-            int kind = sdnn::kKernGather;
-            SDNN_HIP(prof_begin(net, k, kind, &pr));
-            SDNN_HIP(sdnn::launch_spmm_fanin(n, batch, ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
-                                             net->ymax, net->bias_pattern, dense[dc], dense[dc ^ 1], s, &kind));
-            SDNN_HIP(prof_end(net, pr, kind));
-            dc ^= 1;
+        const float *rows;  // Y_{k1}, batch-major
+        bool counted = false;
+        if (plan_resident(net, kd, k1, batch, false, false, &plan)) {
+            // the sparse rows go straight into the product's LDS, and its last launch counts the nonzeros of every row
+            sdnn::ResidentIo io;
+            io.row_ptr = from_user ? y_row_ptr : nullptr;
+            io.cnt_in = from_user ? nullptr : w.cnt[cur ^ 1];
+            io.col = from_user ? y_col : w.col[cur ^ 1];
+            io.val = from_user ? y_val : w.val[cur ^ 1];
+            io.err = net->d_flags;
+            io.y_out = dense[0];
+            io.cnt_out = w.cnt[db];
+            sdnn_status rs = run_resident(net, kd, k1, batch, plan, io, dense);
+            if (rs != SDNN_OK) return rs;
+            rows = dense[0];
+            counted = true;
+        } else {
+            // dense[1] is free until the first layer: it stages the rows batch-major when they hold at least a
+            // quarter of batch * n entries (measured on MI355X: 0.34 instead of 0.69 ms for 32M entries into
+            // 16384 x 4096; at 2% density the extra transpose costs more than the scattered stores it saves)
+            float *stage = nnz_hi >= (double)batch * (double)n / 4.0 ? dense[1] : nullptr;
+            SDNN_HIP(prof_begin(net, -1, sdnn::kKernDensify, &pr));
+            SDNN_HIP(sdnn::launch_densify(n, batch, ld, from_user ? y_row_ptr : nullptr,
+                                          from_user ? nullptr : w.cnt[cur ^ 1], from_user ? y_col : w.col[cur ^ 1],
+                                          from_user ? y_val : w.val[cur ^ 1], dense[0], stage, net->d_flags, s));
+            SDNN_HIP(prof_end(net, pr));
+            for (int32_t k = kd; k < k1; ++k) {
+                const Layer &l = net->layers[(size_t)k];
+                int kind = sdnn::kKernGather;
+                SDNN_HIP(prof_begin(net, k, kind, &pr));
+                SDNN_HIP(sdnn::launch_spmm_fanin(n, batch, ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
+                                                 net->ymax, net->bias_pattern, dense[dc], dense[dc ^ 1], s, &kind));
+                SDNN_HIP(prof_end(net, pr, kind));
+                dc ^= 1;
+            }
+            rows = dense[dc ^ 1];
         }
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernPack, &pr));
-        SDNN_HIP(sdnn::launch_transpose(dense[dc], ld, dense[dc ^ 1], n, n, batch, s));  // -> batch x n
-        if (n % 4 == 0) {
-            // counted first, then packed straight into the other buffer pair (no slot rows in between)
-            SDNN_HIP(sdnn::launch_dense_to_csr(n, batch, dense[dc ^ 1], w.cnt[db ^ 1], out_row_ptr, w.scan_tmp,
-                                               w.col[db ^ 1], w.val[db ^ 1], s));
-            packed = true;
-            outb = db ^ 1;
-        } else {
-            SDNN_HIP(sdnn::launch_dense_to_slots(n, batch, dense[dc ^ 1], w.cnt[db ^ 1], w.col[db ^ 1],
-                                                 w.val[db ^ 1], s));
-            last = db ^ 1;
-            outb = db;
-        }
+        if (!counted) SDNN_HIP(sdnn::launch_transpose(dense[dc], ld, dense[dc ^ 1], n, n, batch, s));  // -> batch x n
+        SDNN_HIP(sdnn::launch_dense_to_csr(n, batch, rows, counted ? w.cnt[db] : w.cnt[db ^ 1], counted, out_row_ptr,
+                                           w.scan_tmp, report, w.col[db ^ 1], w.val[db ^ 1], s));
+        outb = db ^ 1;
         SDNN_HIP(prof_end(net, pr));
     } else {
-        last = cur ^ 1;
+        const int last = cur ^ 1;  // slot buffer holding Y_{k1}
         outb = cur;
-    }
-    if (!packed) {
         int pr = -1;
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernCompact, &pr));
-        SDNN_HIP(sdnn::launch_exclusive_scan_i32_to_i64(batch, w.cnt[last], out_row_ptr, w.scan_tmp, s));
+        SDNN_HIP(sdnn::launch_row_ptr(batch, w.cnt[last], out_row_ptr, w.scan_tmp, report, s));
         SDNN_HIP(sdnn::launch_compact_rows(n, batch, w.cnt[last], out_row_ptr, w.col[last], w.val[last],
                                            w.col[outb], w.val[outb], s));
         SDNN_HIP(prof_end(net, pr));
     }
-    int64_t nnz = 0;
-    uint32_t flags = 0;
-    SDNN_HIP(hipMemcpyAsync(&nnz, out_row_ptr + batch, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    SDNN_HIP(hipMemcpyAsync(&flags, net->d_flags, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     SDNN_HIP(hipStreamSynchronize(s));
+    const int64_t nnz = net->host->nnz;
+    const uint32_t flags = net->host->flags;
     if (flags & 1u)
         return fail(SDNN_ERR_INVALID_INDEX, "Y_in is not valid CSR (row extents or column indices out of range)");
     *out_col = w.col[outb];
@@ -1064,13 +1093,13 @@ sdnn_status sdnn_mxm_csr(sdnn_net net, int32_t k, int32_t semiring, int64_t batc
     const int64_t n = net->n;
     hipStream_t s = net->stream;
     const Layer &l = net->layers[(size_t)k];
-    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, sizeof(uint32_t), s));
+    SDNN_HIP(sdnn::launch_csr_begin(net->d_flags, net->d_stats, 0, y_row_ptr + batch, net->host, s));
     // row by row over the stored entries (the SpGEMM skeleton): Y is never densified
     SDNN_HIP(sdnn::launch_semiring_rows(semiring, n, batch, l.nnz, y_row_ptr, y_col, y_val, l.row_ptr, l.w_pack, Z,
                                         net->d_flags, s));
-    uint32_t flags = 0;
-    SDNN_HIP(hipMemcpyAsync(&flags, net->d_flags, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    SDNN_HIP(sdnn::launch_report(y_row_ptr + batch, sdnn::HostReport{net->host, net->d_flags}, s));
     SDNN_HIP(hipStreamSynchronize(s));
+    const uint32_t flags = net->host->flags;
     if (flags & 1u) return fail(SDNN_ERR_INVALID_INDEX, "Y is not valid CSR (row extents or column indices out of range)");
     return SDNN_OK;
 }
@@ -1108,6 +1137,7 @@ sdnn_status sdnn_net_free(sdnn_net net) {
     (void)hipStreamSynchronize(net->stream);
     prof_clear(net);
     for (hipEvent_t e : net->ev_free) (void)hipEventDestroy(e);
+    (void)hipHostFree(net->host);
     delete net;  // the arena belongs to the caller
     return SDNN_OK;
 }

@@ -815,7 +815,8 @@ hipError_t launch_densify_blocked(int64_t n, int64_t batch, const int64_t *in_ro
 }
 
 hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int32_t *pcnt, int32_t *cnt,
-                                 int64_t *row_ptr, int64_t *scan_tmp, int32_t *out_col, float *out_val, hipStream_t s) {
+                                 int64_t *row_ptr, int64_t *scan_tmp, const HostReport &report, int32_t *out_col,
+                                 float *out_val, hipStream_t s) {
     if (batch == 0) return hipSuccess;
     const int64_t nparts = (n + kPackR - 1) / kPackR;
     const int64_t waves = blocked_chunks(batch) * nparts;
@@ -827,7 +828,7 @@ hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int3
     blocked_scan_kernel<<<(unsigned)((batch + 63) / 64), kScanWaves * 64, 0, s>>>(batch, nparts, pcnt, cnt);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_exclusive_scan_i32_to_i64(batch, cnt, row_ptr, scan_tmp, s);
+    e = launch_row_ptr(batch, cnt, row_ptr, scan_tmp, report, s);
     if (e != hipSuccess) return e;
     static std::atomic<unsigned long long> attr_devices{0};
     e = raise_lds_limit((const void *)blocked_pack_kernel, kPackLds, attr_devices);

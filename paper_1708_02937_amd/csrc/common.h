@@ -65,6 +65,25 @@ hipError_t launch_validate_layer(int64_t n, int64_t nnz, const int64_t *row_ptr,
 hipError_t launch_fanin_counts(int64_t nnz, const int32_t *col, int32_t *counts, hipStream_t s);
 hipError_t launch_exclusive_scan_i32_to_i64(int64_t count, const int32_t *in, int64_t *out, int64_t *tmp,
                                             hipStream_t s);
+// What a CSR forward tells the host, in pinned memory the kernels write to: read after a synchronisation.
+struct HostSlot {
+    int64_t nnz;
+    uint32_t flags;
+    uint32_t pad;
+};
+// Copies *nnz (and *flags, when given) into slot (all null: nothing).
+struct HostReport {
+    HostSlot *slot = nullptr;
+    const uint32_t *flags = nullptr;
+};
+// Row pointers from row counts (out[count] = total), with the total and the flags reported to the host.
+hipError_t launch_row_ptr(int64_t count, const int32_t *in, int64_t *out, int64_t *tmp, const HostReport &report,
+                          hipStream_t s);
+// Start of a CSR forward: clears the flags word and `words` counters, and reports *nnz.
+hipError_t launch_csr_begin(uint32_t *flags, unsigned long long *stats, int64_t words, const int64_t *nnz, HostSlot *slot,
+                            hipStream_t s);
+// Reports *value (and *flags, when given).
+hipError_t launch_report(const int64_t *value, const HostReport &report, hipStream_t s);
 int64_t scan_tmp_elems(int64_t count);
 // Fan-in lists (W_k^T, each list sorted by input index) by a stable radix sort of the entries by column;
 // scratch holds fanin_sort_bytes(nnz) bytes.
@@ -121,10 +140,22 @@ ResidentLayer resident_layer(void *mem, int64_t n, const float *bias);
 // total (device) receives the number of blocks
 hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *total,
                                  hipStream_t s);
+// Input: y_in (batch x n), or sparse rows (caller CSR, extents and columns checked into err; or slot rows with
+// counts: row r at r * n).  Output: y_out, and per sample its nonzeros when cnt_out is not null (one part only).
+struct ResidentIo {
+    const float *y_in = nullptr;
+    const int64_t *row_ptr = nullptr;
+    const int32_t *cnt_in = nullptr;
+    const int32_t *col = nullptr;
+    const float *val = nullptr;
+    uint32_t *err = nullptr;
+    float *y_out = nullptr;
+    int32_t *cnt_out = nullptr;
+};
 // v: samples per workgroup (1, 2 or 4); parts: workgroups the neurons of a sample group are split over (one layer
 // only when above 1).  y_out may equal y_in when parts is 1.
 hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t n, int64_t batch, int v, int parts,
-                                double ymax, int pattern, const float *y_in, float *y_out, hipStream_t s);
+                                double ymax, int pattern, const ResidentIo &io, hipStream_t s);
 // Z = Y (+).(x) W over a semiring (batch-major, no bias or activation; z may equal y when parts is 1).
 hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, int64_t n, int64_t batch, int v, int parts,
                                     const float *y, float *z, hipStream_t s);
@@ -167,12 +198,11 @@ hipError_t launch_spgemm_layer(int64_t n, int64_t batch, const int64_t *in_row_p
 hipError_t launch_densify(int64_t n, int64_t batch, int64_t ld, const int64_t *in_row_ptr, const int32_t *in_cnt,
                           const int32_t *in_col, const float *in_val, float *yt, float *tmp, uint32_t *err,
                           hipStream_t s);
-hipError_t launch_dense_to_slots(int64_t n, int64_t batch, const float *y, int32_t *out_cnt, int32_t *out_col,
-                                 float *out_val, hipStream_t s);
-// Dense batch-major rows (n % 4 == 0) straight to CSR: counts, their exclusive scan into row_ptr[batch + 1],
-// then the survivors of each row at row_ptr[r] in column order.
-hipError_t launch_dense_to_csr(int64_t n, int64_t batch, const float *y, int32_t *cnt, int64_t *row_ptr,
-                               int64_t *scan_tmp, int32_t *out_col, float *out_val, hipStream_t s);
+// Dense batch-major rows straight to CSR: counts (unless cnt holds them already), their exclusive scan into
+// row_ptr[batch + 1], then the survivors of each row at row_ptr[r] in column order.
+hipError_t launch_dense_to_csr(int64_t n, int64_t batch, const float *y, int32_t *cnt, bool counted, int64_t *row_ptr,
+                               int64_t *scan_tmp, const HostReport &report, int32_t *out_col, float *out_val,
+                               hipStream_t s);
 hipError_t launch_compact_rows(int64_t n, int64_t batch, const int32_t *cnt, const int64_t *row_ptr,
                                const int32_t *in_col, const float *in_val, int32_t *out_col, float *out_val,
                                hipStream_t s);
@@ -229,7 +259,8 @@ hipError_t launch_densify_blocked(int64_t n, int64_t batch, const int64_t *in_ro
                                   hipStream_t s);
 // blocked -> CSR: pcnt holds blocked_pack_elems int32, cnt batch int32, row_ptr batch + 1
 hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int32_t *pcnt, int32_t *cnt,
-                                 int64_t *row_ptr, int64_t *scan_tmp, int32_t *out_col, float *out_val, hipStream_t s);
+                                 int64_t *row_ptr, int64_t *scan_tmp, const HostReport &report, int32_t *out_col,
+                                 float *out_val, hipStream_t s);
 // batch-major (row pitch ld) <-> blocked
 hipError_t launch_to_blocked(int64_t n, int64_t batch, int64_t ld_in, const float *y, float *yb, hipStream_t s);
 hipError_t launch_from_blocked(int64_t n, int64_t batch, int64_t ld_out, const float *yb, float *y, hipStream_t s);

@@ -71,31 +71,22 @@ __global__ __launch_bounds__(kRunLen) void resident_order_kernel(int64_t n, cons
     if ((t & 63) == 0) slices[j / 64].y = (l + 3u) / 4u | shortest / 4u << 16;
 }
 
-// First block of every slice (exclusive sums of the block counts) and their total: one workgroup.
-__global__ __launch_bounds__(64) void resident_scan_kernel(int nslices, uint2 *__restrict__ slices,
-                                                           int32_t *__restrict__ total) {
-    uint32_t run = 0;
-    for (int base = 0; base < nslices; base += 64) {
-        const int s = base + (int)threadIdx.x;
-        const uint32_t c = s < nslices ? slices[s].y & 0xffffu : 0u;
-        uint32_t incl = c;
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t v = __shfl_up(incl, d);
-            if ((int)threadIdx.x >= d) incl += v;
-        }
-        if (s < nslices) slices[s].x = run + incl - c;
-        run += __shfl(incl, 63);
-    }
-    if (threadIdx.x == 0) *total = (int32_t)run;
-}
-
-// Blocks of every slice: a wave takes blocks blockIdx.y, + gridDim.y, ... of its slice.
+// Blocks of every slice: a wave takes blocks blockIdx.y, + gridDim.y, ... of its slice.  The slice's first block is
+// the sum of the counts before it, which every wave adds up for itself (at most 80 slices); the first wave of a slice
+// writes it down, the last slice's the total.
 __global__ __launch_bounds__(64) void resident_fill_kernel(int64_t n, const int64_t *__restrict__ fan_ptr,
                                                            const Edge *__restrict__ fan,
-                                                           const uint16_t *__restrict__ order,
-                                                           const uint2 *__restrict__ slices, char *__restrict__ blocks) {
+                                                           const uint16_t *__restrict__ order, uint2 *slices,
+                                                           char *__restrict__ blocks, int32_t *__restrict__ total) {
     const int lane = threadIdx.x;
-    const uint2 sl = slices[blockIdx.x];
+    uint32_t before = 0;
+    for (uint32_t q = lane; q < blockIdx.x; q += 64) before += slices[q].y & 0xffffu;
+    for (int d = 32; d > 0; d >>= 1) before += __shfl_xor(before, d);
+    const uint2 sl = make_uint2(before, slices[blockIdx.x].y);
+    if (lane == 0 && blockIdx.y == 0) {
+        slices[blockIdx.x].x = before;
+        if (blockIdx.x + 1 == gridDim.x) *total = (int32_t)(before + (sl.y & 0xffffu));
+    }
     const uint32_t j = order[(int64_t)blockIdx.x * 64 + lane];
     int64_t e0 = 0;
     uint32_t len = 0;
@@ -234,8 +225,7 @@ struct Slice {
 template <int V, class Op>
 __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs args, int layers, int n, int64_t batch,
                                                                   int nslices, int runs, double ymax,
-                                                                  const float *__restrict__ y_in,
-                                                                  float *__restrict__ y_out) {
+                                                                  ResidentIo io) {
     using Row = typename RowOf<V>::T;
     extern __shared__ __align__(16) char resident_lds[];
     Row *src = reinterpret_cast<Row *>(resident_lds);
@@ -276,14 +266,45 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
 
     Slice next;
     fetch(args.layer[0], run0, next);
+    const bool csr = io.col != nullptr || io.row_ptr != nullptr;
     for (int i = tid; i <= n; i += kRThreads) {
         float y[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) y[v] = (v < rows && i < n) ? y_in[(r0 + v) * n + i] : Op::zero();
+        for (int v = 0; v < V; ++v) y[v] = (!csr && v < rows && i < n) ? io.y_in[(r0 + v) * n + i] : Op::zero();
         src[i] = pack<V>(y);
         // both buffers end in the zero row (with several parts, dst holds one part's outputs and is never read as
         // an input)
         if (i == n && gridDim.y == 1) dst[i] = pack<V>(y);
+    }
+    if (csr) {
+        // sparse rows, placed into the cleared rows: each sample by 16 / V waves, extents and columns checked
+        __syncthreads();
+        const int v = wave % V;
+        const int64_t r = r0 + v;
+        int64_t b = 0, len = 0;
+        if (v < rows) {
+            if (io.row_ptr) {
+                const int64_t nnz = (io.col && io.val) ? io.row_ptr[batch] : 0;
+                b = io.row_ptr[r];
+                len = io.row_ptr[r + 1] - b;
+                if (b < 0 || len < 0 || len > n || b + len > nnz) {
+                    if (lane == 0 && blockIdx.y == 0) atomicOr(io.err, 1u);
+                    len = 0;
+                }
+            } else {
+                b = r * n;
+                len = io.cnt_in[r];
+            }
+        }
+        float *y = reinterpret_cast<float *>(src);
+        for (int64_t t = (int64_t)(wave / V) * 64 + lane; t < len; t += kRThreads / V) {
+            const int32_t i = io.col[b + t];
+            const float f = io.val[b + t];
+            if (i < 0 || i >= n)
+                atomicOr(io.err, 1u);
+            else
+                y[i * V + v] = f;
+        }
     }
     __syncthreads();
 
@@ -371,14 +392,34 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
         src = dst;
         dst = t;
     }
-    // the part's outputs, batch-major
+    // the part's outputs, batch-major, and the nonzeros of each sample (counted in the buffer no one reads any more;
+    // a whole sample's only: one part)
+    int *total = reinterpret_cast<int *>(dst);
+    if (io.cnt_out) {
+        if (tid < V) total[tid] = 0;
+        __syncthreads();
+    }
+    int nonzero[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) nonzero[v] = 0;
     const int count = min(n, run1 * kRunLen) - j0;
     for (int i = tid; i < count; i += kRThreads) {
         float y[V];
         unpack<V>(src[i], y);
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-            if (v < rows) y_out[(r0 + v) * n + j0 + i] = y[v];
+        for (int v = 0; v < V; ++v) {
+            if (v < rows) io.y_out[(r0 + v) * n + j0 + i] = y[v];
+            nonzero[v] += y[v] != 0.0f ? 1 : 0;
+        }
+    }
+    if (io.cnt_out) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            for (int d = 32; d > 0; d >>= 1) nonzero[v] += __shfl_xor(nonzero[v], d);
+            if (lane == 0) atomicAdd(&total[v], nonzero[v]);
+        }
+        __syncthreads();
+        if (tid < rows) io.cnt_out[r0 + tid] = total[tid];
     }
 }
 
@@ -419,11 +460,8 @@ hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *
         n, fan_ptr, const_cast<uint16_t *>(l.order), const_cast<uint2 *>(l.slices));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    resident_scan_kernel<<<1, 64, 0, s>>>((int)slices, const_cast<uint2 *>(l.slices), total);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    resident_fill_kernel<<<dim3((unsigned)slices, 16), 64, 0, s>>>(n, fan_ptr, fan, l.order, l.slices,
-                                                                   const_cast<char *>(l.blocks));
+    resident_fill_kernel<<<dim3((unsigned)slices, 16), 64, 0, s>>>(
+        n, fan_ptr, fan, l.order, const_cast<uint2 *>(l.slices), const_cast<char *>(l.blocks), total);
     return hipGetLastError();
 }
 
@@ -431,7 +469,7 @@ namespace {
 
 template <int V, class Op>
 hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t batch, int parts, double ymax,
-                    const float *y_in, float *y_out, hipStream_t s) {
+                    const ResidentIo &io, hipStream_t s) {
     const int64_t runs = (n + kRunLen - 1) / kRunLen;
     const int per = (int)((runs + parts - 1) / parts);
     parts = (int)((runs + per - 1) / per);
@@ -443,17 +481,17 @@ hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t bat
     const int64_t groups = (batch + V - 1) / V;
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
     spmm_resident_kernel<V, Op><<<dim3((unsigned)groups, (unsigned)parts), kRThreads, lds, s>>>(
-        args, layers, (int)n, batch, (int)((n + 63) / 64), per, ymax, y_in, y_out);
+        args, layers, (int)n, batch, (int)((n + 63) / 64), per, ymax, io);
     return hipGetLastError();
 }
 
 template <class Op>
 hipError_t launch_op(const ResidentArgs &args, int layers, int64_t n, int64_t batch, int v, int parts, double ymax,
-                     const float *y_in, float *y_out, hipStream_t s) {
+                     const ResidentIo &io, hipStream_t s) {
     switch (v) {
-        case 1: return launch_v<1, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 2: return launch_v<2, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
-        case 4: return launch_v<4, Op>(args, layers, n, batch, parts, ymax, y_in, y_out, s);
+        case 1: return launch_v<1, Op>(args, layers, n, batch, parts, ymax, io, s);
+        case 2: return launch_v<2, Op>(args, layers, n, batch, parts, ymax, io, s);
+        case 4: return launch_v<4, Op>(args, layers, n, batch, parts, ymax, io, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -461,13 +499,13 @@ hipError_t launch_op(const ResidentArgs &args, int layers, int64_t n, int64_t ba
 }  // namespace
 
 hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t n, int64_t batch, int v, int parts,
-                                double ymax, int pattern, const float *y_in, float *y_out, hipStream_t s) {
-    if (layers < 1 || layers > kResidentLayers || n > kResidentMaxN || (parts > 1 && layers > 1))
+                                double ymax, int pattern, const ResidentIo &io, hipStream_t s) {
+    if (layers < 1 || layers > kResidentLayers || n > kResidentMaxN || (parts > 1 && (layers > 1 || io.cnt_out)))
         return hipErrorInvalidValue;
     ResidentArgs args;
     for (int k = 0; k < layers; ++k) args.layer[k] = layer[k];
-    return pattern ? launch_op<Forward<true>>(args, layers, n, batch, v, parts, ymax, y_in, y_out, s)
-                   : launch_op<Forward<false>>(args, layers, n, batch, v, parts, ymax, y_in, y_out, s);
+    return pattern ? launch_op<Forward<true>>(args, layers, n, batch, v, parts, ymax, io, s)
+                   : launch_op<Forward<false>>(args, layers, n, batch, v, parts, ymax, io, s);
 }
 
 hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, int64_t n, int64_t batch, int v, int parts,
@@ -475,12 +513,15 @@ hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, in
     if (n > kResidentMaxN) return hipErrorInvalidValue;
     ResidentArgs args;
     args.layer[0] = layer;
+    ResidentIo io;
+    io.y_in = y;
+    io.y_out = z;
     switch (semiring) {
-        case kSemiringPlusTimes: return launch_op<PlusTimes>(args, 1, n, batch, v, parts, 0.0, y, z, s);
-        case kSemiringMaxPlus: return launch_op<MaxPlus>(args, 1, n, batch, v, parts, 0.0, y, z, s);
-        case kSemiringMaxMin: return launch_op<MaxMin>(args, 1, n, batch, v, parts, 0.0, y, z, s);
-        case kSemiringMinMax: return launch_op<MinMax>(args, 1, n, batch, v, parts, 0.0, y, z, s);
-        case kSemiringXorAnd: return launch_op<XorAnd>(args, 1, n, batch, v, parts, 0.0, y, z, s);
+        case kSemiringPlusTimes: return launch_op<PlusTimes>(args, 1, n, batch, v, parts, 0.0, io, s);
+        case kSemiringMaxPlus: return launch_op<MaxPlus>(args, 1, n, batch, v, parts, 0.0, io, s);
+        case kSemiringMaxMin: return launch_op<MaxMin>(args, 1, n, batch, v, parts, 0.0, io, s);
+        case kSemiringMinMax: return launch_op<MinMax>(args, 1, n, batch, v, parts, 0.0, io, s);
+        case kSemiringXorAnd: return launch_op<XorAnd>(args, 1, n, batch, v, parts, 0.0, io, s);
         default: return hipErrorInvalidValue;
     }
 }

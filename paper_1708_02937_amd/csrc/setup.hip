@@ -297,6 +297,68 @@ __global__ void pack_edges_kernel(int64_t nnz, const int32_t *__restrict__ col, 
 
 inline unsigned blocks_for(int64_t count, int threads) { return (unsigned)((count + threads - 1) / threads); }
 
+// Row pointers of a CSR result from its row counts, up to kRowPtrMax rows in one workgroup (four consecutive
+// counts per thread and step): one launch instead of three and the host's copy of the total.
+constexpr int kRowPtrThreads = 1024;
+constexpr int64_t kRowPtrMax = 16384;
+
+__global__ __launch_bounds__(kRowPtrThreads) void row_ptr_kernel(int count, const int32_t *__restrict__ in,
+                                                                 int64_t *__restrict__ out, HostSlot *slot,
+                                                                 const uint32_t *flags) {
+    __shared__ int64_t sums[kRowPtrThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int64_t carry = 0;
+    for (int base = 0; base < count; base += 4 * kRowPtrThreads) {
+        const int i0 = base + 4 * tid;
+        int32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = i0 + u < count ? in[i0 + u] : 0;
+        const int64_t mine = (int64_t)v[0] + v[1] + v[2] + v[3];
+        int64_t incl = mine;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t up = __shfl_up(incl, d);
+            if (lane >= d) incl += up;
+        }
+        if (lane == 63) sums[wave] = incl;
+        __syncthreads();
+        int64_t run = carry + incl - mine, total = 0;
+        for (int w = 0; w < kRowPtrThreads / 64; ++w) {
+            if (w < wave) run += sums[w];
+            total += sums[w];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i0 + u < count) out[i0 + u] = run;
+            run += v[u];
+        }
+        carry += total;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        out[count] = carry;
+        if (slot) {
+            slot->nnz = carry;
+            slot->flags = flags ? *flags : 0u;
+        }
+    }
+}
+
+__global__ void report_kernel(const int64_t *value, HostSlot *slot, const uint32_t *flags) {
+    if (threadIdx.x != 0) return;
+    slot->nnz = *value;
+    slot->flags = flags ? *flags : 0u;
+}
+
+__global__ void csr_begin_kernel(uint32_t *flags, unsigned long long *stats, int64_t words, const int64_t *nnz,
+                                 HostSlot *slot) {
+    for (int64_t t = threadIdx.x; t < words; t += blockDim.x) stats[t] = 0ull;
+    if (threadIdx.x == 0) {
+        *flags = 0u;
+        slot->nnz = *nnz;
+        slot->flags = 0u;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_validate_layer(int64_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
@@ -370,6 +432,28 @@ hipError_t launch_fanin_lists(int64_t n, int64_t nnz, const int64_t *row_ptr, co
 hipError_t launch_pack_edges(int64_t nnz, const int32_t *col, const float *val, Edge *out, hipStream_t s) {
     if (nnz == 0) return hipSuccess;
     pack_edges_kernel<<<blocks_for(nnz, 256), 256, 0, s>>>(nnz, col, val, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_row_ptr(int64_t count, const int32_t *in, int64_t *out, int64_t *tmp, const HostReport &report,
+                          hipStream_t s) {
+    if (count > 0 && count <= kRowPtrMax) {
+        row_ptr_kernel<<<1, kRowPtrThreads, 0, s>>>((int)count, in, out, report.slot, report.flags);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_exclusive_scan_i32_to_i64(count, in, out, tmp, s);
+    if (e != hipSuccess || !report.slot) return e;
+    return launch_report(out + count, report, s);
+}
+
+hipError_t launch_report(const int64_t *value, const HostReport &report, hipStream_t s) {
+    report_kernel<<<1, 64, 0, s>>>(value, report.slot, report.flags);
+    return hipGetLastError();
+}
+
+hipError_t launch_csr_begin(uint32_t *flags, unsigned long long *stats, int64_t words, const int64_t *nnz, HostSlot *slot,
+                            hipStream_t s) {
+    csr_begin_kernel<<<1, 256, 0, s>>>(flags, stats, words, nnz, slot);
     return hipGetLastError();
 }
 

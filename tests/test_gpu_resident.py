@@ -94,3 +94,49 @@ def test_resident_forward_named_in_profiling_log():
     net.free()
     assert [(k, name) for k, name, _ in rec] == [(0, "spmm_resident_kernel"), (1, "spmm_resident_kernel")]
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n,batch,L,lengths,bias_mode", [c for c in CASES if c[2] > 1] + [
+    (40, 4096, 2, [3, 9], 0), (40, 4097, 2, [3, 9], 1), (33, 16384, 2, [5], 0), (33, 16385, 2, [5], 0)])
+def test_resident_csr_forward(n, batch, L, lengths, bias_mode):
+    """A dense enough CSR batch is placed into LDS by the product itself, and the result's row counts come from its
+    last launch (row pointers in one workgroup up to 16384 rows, by the general scan beyond); empty rows among them."""
+    import paper_1708_02937_amd as sd
+
+    p = _problem(n, batch, L, lengths, n + batch)
+    p.y0_dense[::7] = 0.0
+    print("[case] resident csr", n, batch, L, bias_mode, flush=True)
+    net = sd.net_from_problem(p, bias_mode=bias_mode)
+    got = tuple(x.cpu().numpy() for x in net.forward_csr(*p.y0_as_csr()))
+    net.free()
+    parity.compare(p, got, bias_mode=bias_mode)
+
+
+@pytest.mark.parametrize("batch", [3, 300, 1030])
+def test_resident_csr_forward_checks_its_input(batch):
+    """Row extents and columns out of range are reported, whichever sample of a workgroup's they are in, and rows
+    that are all empty need no column or value array."""
+    import paper_1708_02937_amd as sd
+
+    p = _problem(500, batch, 2, [3, 9], 4)
+    net = sd.net_from_problem(p)
+    rp, c, v = p.y0_as_csr()
+    for r in (0, 1, batch // 2, batch - 1):
+        for at, wrong in ((rp[r], -1), (rp[r + 1] - 1, p.n), (rp[r], 1 << 30)):
+            bad = c.copy()
+            bad[at] = wrong
+            print("[case] resident csr check", batch, r, wrong, flush=True)
+            with pytest.raises(sd.SdnnError) as e:
+                net.forward_csr(rp, bad, v)
+            assert e.value.name == "SDNN_ERR_INVALID_INDEX"
+    bad = rp.copy()
+    bad[1] = bad[2] + 1
+    with pytest.raises(sd.SdnnError) as e:
+        net.forward_csr(bad, c, v)
+    assert e.value.name == "SDNN_ERR_INVALID_INDEX"
+    got = tuple(x.cpu().numpy() for x in net.forward_csr(rp, c, v))
+    parity.compare(p, got)
+    p.y0_dense[:] = 0.0
+    got = tuple(x.cpu().numpy() for x in net.forward_csr(np.zeros(batch + 1, np.int64), c[:0], v[:0]))
+    net.free()
+    parity.compare(p, got)
