@@ -228,7 +228,8 @@ sdnn_status sdnn_forward_dense(sdnn_net net, int32_t k0, int32_t k1, int64_t bat
  * activation buffers and the dense arm's partial sums) is a fixed device array of the library, one per
  * GPU, sdnn_noalloc_scratch_bytes() bytes (64 MiB), held from the first sdnn_net_create on that GPU until
  * the process ends.  The call itself allocates and frees nothing.  Layers whose workspace
- * (sdnn_workspace_size(net, batch, 0)) exceeds that size are refused with UNSUPPORTED.  Every call on one
+ * (sdnn_workspace_size(net, batch, 0), its rounding of the batch to a multiple of four aside) exceeds that size are
+ * refused with UNSUPPORTED.  Every call on one
  * GPU shares the array, which keeps the last call's contents: calls that overlap on one GPU (other host
  * threads, other nets or streams without ordering between them) race and give undefined results.  Same
  * arguments, result and errors as sdnn_forward_dense otherwise.

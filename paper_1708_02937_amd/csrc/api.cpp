@@ -221,14 +221,15 @@ CsrWs carve_csr(void *base, int64_t n, int64_t batch) {
 
 constexpr int64_t kMaxScan = 16777216;  // longest array the device prefix sum handles (fan-in pointers, row pointers)
 
-// bytes of one n x batch fp32 activation buffer at row pitch act_ld(n, batch)
-size_t act_bytes(int64_t n, int64_t batch) {
-    return align_up((size_t)n * (size_t)sdnn::act_ld(n, batch) * sizeof(float));
-}
+// bytes of one neuron-major activation buffer at row pitch ld
+size_t act_bytes(int64_t n, int64_t ld) { return align_up((size_t)n * (size_t)ld * sizeof(float)); }
 
 // two activation buffers, then the dense arm's split-K partial sums (small batches only)
+size_t dense_ws_bytes(int64_t n, int64_t batch, int64_t ld, int num_cu) {
+    return 2 * act_bytes(n, ld) + align_up(sdnn::gemm_partial_bytes(n, batch, num_cu));
+}
 size_t dense_ws_bytes(int64_t n, int64_t batch, int num_cu) {
-    return 2 * act_bytes(n, batch) + align_up(sdnn::gemm_partial_bytes(n, batch, num_cu));
+    return dense_ws_bytes(n, batch, sdnn::act_ld(n, batch), num_cu);
 }
 
 // Workspace of sdnn_forward_dense_noalloc: a fixed device array, one copy per GPU, held until the process
@@ -316,8 +317,10 @@ struct ResidentPlan {
 // over, and the neurons split over workgroups (then a launch per layer) where a small batch leaves CUs idle: one
 // layer of 4096 neurons and 64 entries each at batch 64 takes 23.7 us whole and 9.2 in four parts, four layers of
 // 1024 neurons and 16 entries 11.5 us fused and 18 launch by launch.  The neuron-major products move 4 bytes
-// per product from L2 (about 27 TB/s with four samples per lane, from batch 256 on, and 12 below) and cost 6 us
-// per layer and two transposes; they win only where the last round of workgroups is nearly empty.  With profiling on every layer is a launch of its own, and ranges with a
+// per product from L2 (about 27 TB/s with four samples per lane, from batch 256 on, and 12 to 16 below) and cost 6 us
+// per layer and two transposes; they win only where the last round of workgroups is nearly empty.  The LDS-tiled
+// product of high fan-in layers takes 1.76 + 1.21 density us per tile of 16 inputs and round of workgroups (64 neurons
+// x 256 samples): 157 us per layer at n 1000, batch 129, where the resident product takes 40.  With profiling on every layer is a launch of its own, and ranges with a
 // layer of under 2^24 products stay on the neuron-major products: the one launch is what they gain from.
 bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, bool semiring,
                    ResidentPlan *plan) {
@@ -328,10 +331,15 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
         const Layer &l = net->layers[(size_t)k];
         const double products = (double)l.nnz * (double)batch;
         if (!l.resident) return false;
-        // (a semiring multiply is not logged, and high fan-in forwards have a product of their own)
-        if (!semiring && ((net->profiling && products < (double)(1 << 24)) || (l.tile_mask && batch >= 128))) return false;
+        if (!semiring && net->profiling && products < (double)(1 << 24)) return false;  // (semirings are not logged)
         blocks += (double)l.resident_blocks;
-        gather += 6.0 + products / (batch >= 256 && batch % 4 == 0 ? 6.75e6 : 3.0e6);
+        if (!semiring && l.slots && batch > 124) {
+            const double tiles = std::ceil((double)n / 16.0);
+            gather += 6.0 + std::ceil(std::ceil((double)n / 64.0) * std::ceil((double)batch / 256.0) / (double)net->num_cu) *
+                                tiles * (1.76 + 1.21 * (double)l.nnz / ((double)n * (double)n));
+        } else {
+            gather += 6.0 + products / (batch > 252 ? 6.75e6 : n >= 4096 ? 4.1e6 : 3.0e6);
+        }
     }
     const int64_t runs = (n + 1023) / 1024;
     const double layers = (double)(k1 - k0), cus = (double)net->num_cu;
@@ -719,21 +727,24 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             SDNN_HIP(hipMemcpyAsync(Y_out, Y_in, (size_t)batch * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
         return SDNN_OK;
     }
+    int64_t ld = sdnn::act_ld(n, batch);
     if (static_ws) {
         // the library's fixed scratch array of this device replaces the caller's workspace
         const ScratchSlot *slot = net->device < kMaxDevices ? &g_scratch[net->device] : nullptr;
         if (!slot || !slot->ptr)
             return fail(SDNN_ERR_DEVICE, std::string("scratch array of the allocation-free entry point unavailable: ") +
                                              hipGetErrorString(slot ? slot->err : hipErrorInvalidDevice));
-        if (dense_ws_bytes(n, batch, net->num_cu) > kScratchBytes)
-            return fail(SDNN_ERR_UNSUPPORTED, "batch x n needs " + std::to_string(dense_ws_bytes(n, batch, net->num_cu)) +
+        if (dense_ws_bytes(n, batch, net->num_cu) > kScratchBytes) ld = sdnn::act_ld_tight(n, batch);
+        const size_t need = dense_ws_bytes(n, batch, ld, net->num_cu);
+        if (need > kScratchBytes)
+            return fail(SDNN_ERR_UNSUPPORTED, "batch x n needs " + std::to_string(need) +
                                                   " bytes of scratch; the allocation-free entry point holds " +
                                                   std::to_string(kScratchBytes));
         ws = slot->ptr;
         ws_bytes = (int64_t)kScratchBytes;
     }
     if (!ws) return fail(SDNN_ERR_NULL_POINTER, "ws is required");
-    if (ws_bytes < (int64_t)dense_ws_bytes(n, batch, net->num_cu))
+    if (ws_bytes < (int64_t)dense_ws_bytes(n, batch, ld, net->num_cu))
         return fail(SDNN_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than sdnn_workspace_size(net, batch, 0)");
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
@@ -741,11 +752,10 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             return fail(SDNN_ERR_INVALID_OBJECT, "dense arm requested before sdnn_net_build_dense (or without its copy "
                                                  "in the arena)");
     }
-    const int64_t ld = sdnn::act_ld(n, batch);
     float *buf[2];
     buf[0] = (float *)ws;
-    buf[1] = (float *)((char *)ws + act_bytes(n, batch));
-    double *partial = (double *)((char *)ws + 2 * act_bytes(n, batch));
+    buf[1] = (float *)((char *)ws + act_bytes(n, ld));
+    double *partial = (double *)((char *)ws + 2 * act_bytes(n, ld));
     int pr = -1;
     if (arm == SDNN_ARM_SPARSE && use_blocked(net, k0, k1, batch)) {
         // the sample-blocked layout (each buffer holds n x ld >= n x round32(batch) floats)
@@ -784,8 +794,8 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         int kind = sdnn::kKernDenseGemm;
         SDNN_HIP(prof_begin(net, k, kind, &pr));
         if (arm == SDNN_ARM_SPARSE)
-            SDNN_HIP(sdnn::launch_spmm_fanin(n, batch, ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
-                                             net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
+            SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask, l.slots,
+                                             l.bias, net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
         else if (arm == SDNN_ARM_DENSE)
             SDNN_HIP(sdnn::launch_gemm_dense_layer(n, batch, ld, l.dense_wt, l.bias, net->ymax, buf[cur],
                                                    buf[cur ^ 1], partial, net->num_cu, s));
@@ -1007,8 +1017,9 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
                 const Layer &l = net->layers[(size_t)k];
                 int kind = sdnn::kKernGather;
                 SDNN_HIP(prof_begin(net, k, kind, &pr));
-                SDNN_HIP(sdnn::launch_spmm_fanin(n, batch, ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
-                                                 net->ymax, net->bias_pattern, dense[dc], dense[dc ^ 1], s, &kind));
+                SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask,
+                                                 l.slots, l.bias, net->ymax, net->bias_pattern, dense[dc],
+                                                 dense[dc ^ 1], s, &kind));
                 SDNN_HIP(prof_end(net, pr, kind));
                 dc ^= 1;
             }
@@ -1074,9 +1085,9 @@ sdnn_status sdnn_mxm_dense(sdnn_net net, int32_t k, int32_t semiring, int64_t ba
     }
     const int64_t ld = sdnn::act_ld(n, batch);
     float *yt = (float *)ws;
-    float *zt = (float *)((char *)ws + act_bytes(n, batch));
+    float *zt = (float *)((char *)ws + act_bytes(n, ld));
     SDNN_HIP(sdnn::launch_transpose(Y, n, yt, ld, batch, n, s));  // batch x n -> n x batch
-    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, batch, ld, l.fan_ptr, l.fan, yt, zt, s));
+    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, yt, zt, s));
     SDNN_HIP(sdnn::launch_transpose(zt, ld, Z, n, n, batch, s));  // n x batch -> batch x n
     return SDNN_OK;
 }

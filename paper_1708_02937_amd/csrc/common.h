@@ -97,10 +97,22 @@ hipError_t launch_pack_edges(int64_t nnz, const int32_t *col, const float *val, 
 // per row at a power-of-two byte pitch fall into a fraction of an XCD's L2 sets (measured on MI355X: at a
 // 16 KiB pitch a 1 MiB working set already misses about half the time, at 16 KiB + 256 B a 3 MiB one stays
 // resident), so for wide layers (n > 4096) of 256 samples or more the pitch is an odd multiple of 64 floats
-// (256 bytes).  At n = 4096, batch 1024 the padding measured 1-3% slower per layer, so narrower layers keep
-// the dense pitch.
+// (256 bytes).  At n = 4096, batch 1024 the padding measured 1-3% slower per layer, so narrower layers and
+// smaller batches keep the dense pitch, rounded up to whole 16-byte loads.
 inline int64_t act_ld(int64_t n, int64_t batch) {
-    return (n <= 4096 || batch < 256) ? batch : (((batch + 63) / 64) | 1) * 64;
+    return (n <= 4096 || batch < 256) ? (batch + 3) / 4 * 4 : (((batch + 63) / 64) | 1) * 64;
+}
+// The same without the rounding, for a workspace that has no room for it.
+inline int64_t act_ld_tight(int64_t n, int64_t batch) {
+    return (n <= 4096 || batch < 256) ? batch : act_ld(n, batch);
+}
+// Samples the neuron-major products compute: the batch rounded up to a multiple of four when the pitch has room.
+// The samples past the batch hold whatever the buffer held and are not copied out; a sample depends on no other.
+// (An odd batch otherwise gathers one column per lane: n 9001, 60 entries per neuron, batch 333, four layers took 318 us
+// that way, 198 this.)
+inline int64_t act_batch(int64_t batch, int64_t ld) {
+    const int64_t b = (batch + 3) / 4 * 4;
+    return b <= ld ? b : batch;
 }
 
 // spmm.hip

@@ -140,3 +140,68 @@ def test_resident_csr_forward_checks_its_input(batch):
     got = tuple(x.cpu().numpy() for x in net.forward_csr(np.zeros(batch + 1, np.int64), c[:0], v[:0]))
     net.free()
     parity.compare(p, got)
+
+
+@pytest.mark.parametrize("n,batch,d", [(1000, 125, 0.6), (1000, 129, 0.6), (3000, 253, 0.3), (4100, 131, 0.5),
+                                       (2049, 1, 0.99), (600, 1027, 0.9)])
+def test_high_fan_in_ragged_batches(n, batch, d):
+    """Layers of density 2/9 and more at batches that are no multiple of four: the resident product or, with the batch
+    rounded up inside the workspace, the LDS-tiled one; one row per sample compared, integer values bit for bit."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+    from workloads import integer_shadow, tiny_random
+
+    p = tiny_random(n, n, 1, batch, w_density=d, y_density=0.7, dense_input=True, bias_lo=-1.0, bias_hi=1.0)
+    p = integer_shadow(p)
+    net = sd.net_from_problem(p)
+    print("[case] high fan-in ragged", n, batch, d, flush=True)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    got = net.forward_dense(y).cpu().numpy()
+    net.set_profiling(True)
+    other = net.forward_dense(y).cpu().numpy()
+    net.free()
+    assert got.tobytes() == other.tobytes()
+    rows = np.arange(0, batch, 1 + batch // 40)
+    parity.compare(p, dense_to_csr(got[rows]), rows=rows, exact=True)
+
+
+@pytest.mark.parametrize("n,batch", [(5120, 1), (6000, 5), (9001, 33), (8200, 259), (12000, 331)])
+def test_wide_layers_ragged_batches(n, batch):
+    """Layers too wide for the resident product at batches that are no multiple of four (rounded up inside the
+    workspace), dense and CSR input, and on the fixed scratch array."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = _problem(n, batch, 2, [60, 0, 90, 64], n)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    print("[case] wide ragged", n, batch, flush=True)
+    got = net.forward_dense(y)
+    parity.compare(p, dense_to_csr(got.cpu().numpy()))
+    parity.compare(p, tuple(x.cpu().numpy() for x in net.forward_csr(*p.y0_as_csr())))
+    out = torch.empty_like(y)
+    sd.sdnn_forward_dense_noalloc(net.handle, 0, p.L, batch, y, out, sd.SDNN_ARM_SPARSE)
+    assert torch.equal(out, got)
+    net.free()
+
+
+def test_scratch_array_without_room_for_rounding():
+    """The fixed scratch array takes a batch whose two buffers fit only without the batch rounded up to four: the
+    products then run at the batch as it is."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    n = 40009
+    batch = sd.sdnn_noalloc_scratch_bytes() // (2 * 4 * n)
+    assert batch % 4 == 1 and 2 * 4 * n * (batch + 3) > sd.sdnn_noalloc_scratch_bytes()
+    p = _problem(n, batch, 1, [3, 0, 5], 8)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    print("[case] scratch array", n, batch, flush=True)
+    out = torch.empty_like(y)
+    sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, y, out, sd.SDNN_ARM_SPARSE)
+    assert torch.equal(out, net.forward_dense(y))
+    net.free()
