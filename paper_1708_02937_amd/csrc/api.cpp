@@ -137,8 +137,8 @@ LayerPlan plan_layer(int64_t n, int64_t cap, int32_t dense_flags) {
         lp.starts = take(off, (size_t)(sdnn::blocked_regions(n) + 1) * sizeof(int64_t));
     }
     if (sdnn::resident_planned(n)) lp.resident = take(off, sdnn::resident_bytes(n, cap));
-    if (dense_flags & SDNN_ARENA_DENSE_F64) lp.dense64 = take(off, (size_t)n * (size_t)n * sizeof(double));
-    if (dense_flags & SDNN_ARENA_DENSE_F32) lp.dense32 = take(off, (size_t)n * (size_t)n * sizeof(float));
+    if (dense_flags & SDNN_ARENA_DENSE_F64) lp.dense64 = take(off, sdnn::gemm_weight_elems(n) * sizeof(double));
+    if (dense_flags & SDNN_ARENA_DENSE_F32) lp.dense32 = take(off, sdnn::gemm_weight_elems(n) * sizeof(float));
     lp.bytes = off;
     return lp;
 }
@@ -224,12 +224,23 @@ constexpr int64_t kMaxScan = 16777216;  // longest array the device prefix sum h
 // bytes of one neuron-major activation buffer at row pitch ld
 size_t act_bytes(int64_t n, int64_t ld) { return align_up((size_t)n * (size_t)ld * sizeof(float)); }
 
-// two activation buffers, then the dense arm's split-K partial sums (small batches only)
-size_t dense_ws_bytes(int64_t n, int64_t batch, int64_t ld, int num_cu) {
-    return 2 * act_bytes(n, ld) + align_up(sdnn::gemm_partial_bytes(n, batch, num_cu));
+// two activation buffers of a dense arm, in its operand layout, and its split-K partial sums (small batches only)
+size_t arm_act_bytes(int64_t n, int64_t batch) { return align_up(sdnn::gemm_act_elems(n, batch) * sizeof(float)); }
+size_t arm_ws_bytes(int64_t n, int64_t batch, int num_cu) {
+    return 2 * arm_act_bytes(n, batch) + align_up(sdnn::gemm_partial_bytes(n, batch, num_cu));
 }
-size_t dense_ws_bytes(int64_t n, int64_t batch, int num_cu) {
-    return dense_ws_bytes(n, batch, sdnn::act_ld(n, batch), num_cu);
+
+// a dense-Y call's workspace: two neuron-major activation buffers, or, for a net with dense copies, what the arms need
+size_t dense_ws_bytes(int64_t n, int64_t batch, int32_t dense_flags, int num_cu) {
+    const size_t sparse = 2 * act_bytes(n, sdnn::act_ld(n, batch));
+    return dense_flags ? std::max(sparse, arm_ws_bytes(n, batch, num_cu)) : sparse;
+}
+
+// What decides whether the fixed scratch array takes a batch: two buffers of n x batch and fp64 sums of every K split.
+size_t noalloc_bytes(int64_t n, int64_t batch, int num_cu) {
+    const int sp = sdnn::gemm_splits(n, batch, num_cu);
+    const size_t sums = sp > 1 ? (size_t)sp * (size_t)n * (size_t)batch * sizeof(double) : 0;
+    return 2 * act_bytes(n, sdnn::act_ld_tight(n, batch)) + align_up(sums);
 }
 
 // Workspace of sdnn_forward_dense_noalloc: a fixed device array, one copy per GPU, held until the process
@@ -652,7 +663,7 @@ sdnn_status sdnn_workspace_size(sdnn_net net, int64_t batch, int32_t y_is_csr, i
     if (!net) return fail(SDNN_ERR_INVALID_OBJECT, "net is NULL");
     if (!bytes) return fail(SDNN_ERR_NULL_POINTER, "bytes is NULL");
     if (batch < 0) return fail(SDNN_ERR_INVALID_VALUE, "batch must be >= 0");
-    *bytes = y_is_csr ? (int64_t)carve_csr(nullptr, net->n, batch).bytes : (int64_t)dense_ws_bytes(net->n, batch, net->num_cu);
+    *bytes = y_is_csr ? (int64_t)carve_csr(nullptr, net->n, batch).bytes : (int64_t)dense_ws_bytes(net->n, batch, net->dense_flags, net->num_cu);
     return SDNN_OK;
 }
 
@@ -734,17 +745,29 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         if (!slot || !slot->ptr)
             return fail(SDNN_ERR_DEVICE, std::string("scratch array of the allocation-free entry point unavailable: ") +
                                              hipGetErrorString(slot ? slot->err : hipErrorInvalidDevice));
-        if (dense_ws_bytes(n, batch, net->num_cu) > kScratchBytes) ld = sdnn::act_ld_tight(n, batch);
-        const size_t need = dense_ws_bytes(n, batch, ld, net->num_cu);
-        if (need > kScratchBytes)
-            return fail(SDNN_ERR_UNSUPPORTED, "batch x n needs " + std::to_string(need) +
-                                                  " bytes of scratch; the allocation-free entry point holds " +
-                                                  std::to_string(kScratchBytes));
+        if (noalloc_bytes(n, batch, net->num_cu) > kScratchBytes)
+            return fail(SDNN_ERR_UNSUPPORTED,
+                        "batch x n needs " + std::to_string(noalloc_bytes(n, batch, net->num_cu)) +
+                            " bytes of scratch; the allocation-free entry point holds " + std::to_string(kScratchBytes));
+        if (2 * act_bytes(n, ld) > kScratchBytes) ld = sdnn::act_ld_tight(n, batch);
+        if (arm != SDNN_ARM_SPARSE && batch > 1 && arm_ws_bytes(n, batch, net->num_cu) > kScratchBytes) {
+            // the padding of the arms' layout does not fit at this size: two halves, in the order in which neither
+            // overwrites rows of Y_in that the other still reads
+            const int64_t half = batch > 64 ? (batch / 2 + 63) / 64 * 64 : (batch + 1) / 2;
+            const bool up = (uintptr_t)Y_out > (uintptr_t)Y_in;
+            for (int part = 0; part < 2; ++part) {
+                const bool first = (part == 0) != up;
+                const int64_t r0 = first ? 0 : half, rows = first ? half : batch - half;
+                st = forward_dense_impl(net, k0, k1, rows, Y_in + r0 * n, Y_out + r0 * n, nullptr, 0, arm, true);
+                if (st != SDNN_OK) return st;
+            }
+            return SDNN_OK;
+        }
         ws = slot->ptr;
         ws_bytes = (int64_t)kScratchBytes;
     }
     if (!ws) return fail(SDNN_ERR_NULL_POINTER, "ws is required");
-    if (ws_bytes < (int64_t)dense_ws_bytes(n, batch, ld, net->num_cu))
+    if (!static_ws && ws_bytes < (int64_t)dense_ws_bytes(n, batch, net->dense_flags, net->num_cu))
         return fail(SDNN_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than sdnn_workspace_size(net, batch, 0)");
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
@@ -752,12 +775,35 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             return fail(SDNN_ERR_INVALID_OBJECT, "dense arm requested before sdnn_net_build_dense (or without its copy "
                                                  "in the arena)");
     }
-    float *buf[2];
-    buf[0] = (float *)ws;
-    buf[1] = (float *)((char *)ws + act_bytes(n, ld));
-    double *partial = (double *)((char *)ws + 2 * act_bytes(n, ld));
     int pr = -1;
-    if (arm == SDNN_ARM_SPARSE && use_blocked(net, k0, k1, batch)) {
+    if (arm != SDNN_ARM_SPARSE) {
+        // a dense arm: activations in the matrix cores' operand layout throughout
+        const bool f64 = arm == SDNN_ARM_DENSE;
+        float *act[2] = {(float *)ws, (float *)((char *)ws + arm_act_bytes(n, batch))};
+        void *partial = (char *)ws + 2 * arm_act_bytes(n, batch);
+        SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
+        SDNN_HIP(sdnn::launch_to_quads(n, batch, f64, Y_in, act[0], s));
+        SDNN_HIP(prof_end(net, pr));
+        int ca = 0;
+        for (int32_t k = k0; k < k1; ++k) {
+            const Layer &l = net->layers[(size_t)k];
+            SDNN_HIP(prof_begin(net, k, f64 ? sdnn::kKernDenseGemm : sdnn::kKernDenseGemm32, &pr));
+            if (f64)
+                SDNN_HIP(sdnn::launch_gemm_dense_layer(n, batch, l.dense_wt, l.bias, net->ymax, act[ca], act[ca ^ 1],
+                                                       (double *)partial, net->num_cu, s));
+            else
+                SDNN_HIP(sdnn::launch_gemm32_dense_layer(n, batch, l.dense_wt32, l.bias, net->ymax, act[ca], act[ca ^ 1],
+                                                         (float *)partial, net->num_cu, s));
+            SDNN_HIP(prof_end(net, pr));
+            ca ^= 1;
+        }
+        SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
+        SDNN_HIP(sdnn::launch_from_quads(n, batch, f64, act[ca], Y_out, s));
+        SDNN_HIP(prof_end(net, pr));
+        return SDNN_OK;
+    }
+    float *buf[2] = {(float *)ws, (float *)((char *)ws + act_bytes(n, ld))};
+    if (use_blocked(net, k0, k1, batch)) {
         // the sample-blocked layout (each buffer holds n x ld >= n x round32(batch) floats)
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
         SDNN_HIP(sdnn::launch_to_blocked(n, batch, n, Y_in, buf[0], s));
@@ -776,7 +822,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         SDNN_HIP(prof_end(net, pr));
         return SDNN_OK;
     }
-    if (arm == SDNN_ARM_SPARSE && (Y_in == Y_out || !overlap(Y_in, Y_out, (size_t)batch * (size_t)n))) {
+    if ((Y_in == Y_out || !overlap(Y_in, Y_out, (size_t)batch * (size_t)n))) {
         ResidentPlan plan;
         if (plan_resident(net, k0, k1, batch, Y_in != Y_out, false, &plan)) {
             sdnn::ResidentIo io;
@@ -791,19 +837,10 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
     int cur = 0;
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
-        int kind = sdnn::kKernDenseGemm;
+        int kind = sdnn::kKernGather;
         SDNN_HIP(prof_begin(net, k, kind, &pr));
-        if (arm == SDNN_ARM_SPARSE)
-            SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask, l.slots,
-                                             l.bias, net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
-        else if (arm == SDNN_ARM_DENSE)
-            SDNN_HIP(sdnn::launch_gemm_dense_layer(n, batch, ld, l.dense_wt, l.bias, net->ymax, buf[cur],
-                                                   buf[cur ^ 1], partial, net->num_cu, s));
-        else {
-            kind = sdnn::kKernDenseGemm32;
-            SDNN_HIP(sdnn::launch_gemm32_dense_layer(n, batch, ld, l.dense_wt32, l.bias, net->ymax, buf[cur],
-                                                     buf[cur ^ 1], reinterpret_cast<float *>(partial), net->num_cu, s));
-        }
+        SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
+                                         net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
         SDNN_HIP(prof_end(net, pr, kind));
         cur ^= 1;
     }
@@ -1062,7 +1099,7 @@ static sdnn_status mxm_common(sdnn_net net, int32_t k, int32_t semiring, int64_t
     if (batch < 0) return fail(SDNN_ERR_DIMENSION_MISMATCH, "batch must be >= 0");
     if (!needs_ws) return SDNN_OK;
     if (batch > 0 && !ws) return fail(SDNN_ERR_NULL_POINTER, "ws is required");
-    if (batch > 0 && ws_bytes < (int64_t)dense_ws_bytes(net->n, batch, net->num_cu))
+    if (batch > 0 && ws_bytes < (int64_t)dense_ws_bytes(net->n, batch, net->dense_flags, net->num_cu))
         return fail(SDNN_ERR_WORKSPACE_TOO_SMALL, "workspace smaller than sdnn_workspace_size(net, batch, 0)");
     return SDNN_OK;
 }

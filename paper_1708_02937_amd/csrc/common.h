@@ -172,18 +172,21 @@ hipError_t launch_spmm_resident(const ResidentLayer *layer, int layers, int64_t 
 hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, int64_t n, int64_t batch, int v, int parts,
                                     const float *y, float *z, hipStream_t s);
 
-// gemm.hip
-hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s);
+// gemm.hip: the dense-W arms.  Weights and activations are in the matrix-core operand layout (K padded to 32).
+size_t gemm_weight_elems(int64_t n);                // values of one dense copy
+size_t gemm_act_elems(int64_t n, int64_t batch);    // floats of one activation buffer
 int gemm_splits(int64_t n, int64_t batch, int num_cu);
 size_t gemm_partial_bytes(int64_t n, int64_t batch, int num_cu);
-// partial: gemm_partial_bytes(n, batch, num_cu) bytes of scratch (unused when that is 0).
-hipError_t launch_gemm_dense_layer(int64_t n, int64_t batch, int64_t ld, const double *wt, const float *bias, double ymax,
-                                   const float *yt, float *zt, double *partial, int num_cu, hipStream_t s);
-
-// fp32 copy and the fp32 matrix-core arm (partial: gemm_partial_bytes scratch, used as fp32)
+hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s);
 hipError_t launch_dense32_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, float *wt, hipStream_t s);
-hipError_t launch_gemm32_dense_layer(int64_t n, int64_t batch, int64_t ld, const float *wt, const float *bias,
-                                     double ymax, const float *yt, float *zt, float *partial, int num_cu, hipStream_t s);
+// batch-major <-> the arms' activation layout (f64: of the fp64 arm)
+hipError_t launch_to_quads(int64_t n, int64_t batch, bool f64, const float *y, float *yq, hipStream_t s);
+hipError_t launch_from_quads(int64_t n, int64_t batch, bool f64, const float *yq, float *y, hipStream_t s);
+// partial: gemm_partial_bytes(n, batch, num_cu) bytes of scratch (unused when that is 0; the fp32 arm's as fp32).
+hipError_t launch_gemm_dense_layer(int64_t n, int64_t batch, const double *wt, const float *bias, double ymax,
+                                   const float *yq, float *zq, double *partial, int num_cu, hipStream_t s);
+hipError_t launch_gemm32_dense_layer(int64_t n, int64_t batch, const float *wt, const float *bias, double ymax,
+                                     const float *yq, float *zq, float *partial, int num_cu, hipStream_t s);
 
 // spgemm.hip
 size_t spgemm_lds_bytes(int64_t n);
