@@ -813,7 +813,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             const Layer &l = net->layers[(size_t)k];
             SDNN_HIP(prof_begin(net, k, sdnn::kKernBlocked, &pr));
             SDNN_HIP(sdnn::launch_spmm_blocked(n, batch, l.sched, l.stage, l.regions, nullptr, l.bias, net->ymax, net->bias_pattern, buf[cb],
-                                               buf[cb ^ 1], s));
+                                               buf[cb ^ 1], nullptr, s));
             SDNN_HIP(prof_end(net, pr));
             cb ^= 1;
         }
@@ -1002,16 +1002,20 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
                                               dense[0], nz, net->d_flags, s));
         SDNN_HIP(prof_end(net, pr));
         int dc = 0;
+        // the last product counts its nonzeros for the packing, into the value buffer the packed rows go to (at least
+        // n * round64(batch) floats, an eighth of it used; free until then)
+        uint8_t *counts = net->layers[(size_t)(k1 - 1)].regions ? reinterpret_cast<uint8_t *>(w.val[db ^ 1]) : nullptr;
         for (int32_t k = kd; k < k1; ++k) {
             const Layer &l = net->layers[(size_t)k];
             SDNN_HIP(prof_begin(net, k, sdnn::kKernBlocked, &pr));
             SDNN_HIP(sdnn::launch_spmm_blocked(n, batch, l.sched, l.stage, l.regions, k == kd ? nz : nullptr, l.bias,
-                                               net->ymax, net->bias_pattern, dense[dc], dense[dc ^ 1], s));
+                                               net->ymax, net->bias_pattern, dense[dc], dense[dc ^ 1],
+                                               k + 1 == k1 ? counts : nullptr, s));
             SDNN_HIP(prof_end(net, pr));
             dc ^= 1;
         }
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernPack, &pr));
-        SDNN_HIP(sdnn::launch_blocked_to_csr(n, batch, dense[dc], w.pcnt, w.cnt[db ^ 1], out_row_ptr, w.scan_tmp, report,
+        SDNN_HIP(sdnn::launch_blocked_to_csr(n, batch, dense[dc], counts, w.pcnt, w.cnt[db ^ 1], out_row_ptr, w.scan_tmp, report,
                                              w.col[db ^ 1], w.val[db ^ 1], s));
         SDNN_HIP(prof_end(net, pr));
         outb = db ^ 1;

@@ -39,6 +39,12 @@ constexpr int kBTile = kBWaves * kBGroups * 8;  // neurons per workgroup and chu
 #define SDNN_BLOCKED_UNROLL 8
 #endif
 constexpr int kBUnroll = SDNN_BLOCKED_UNROLL;  // list entries per block (rows in flight per lane)
+constexpr int kPackR = 512;       // neurons per part of the blocked -> CSR packing
+constexpr int kRunParts = kSortSeg / kPackR;       // parts of a run of the schedule's sort
+constexpr int kRunTiles = kSortSeg / kBTile;       // workgroups of the product per run
+constexpr int kGroupCounts = kRunParts * kBW;      // counts a workgroup of the product writes, one byte each
+static_assert(kGroupCounts == kBWaves * 64 && kBTile < 256, "one byte and one thread per count");
+static_assert(kBGroups <= 4 && kRunParts <= 16, "a byte per group of a wave holds its outputs' part and pattern");
 constexpr int kStageCap = 4096;  // entries of a workgroup's staged lists (32 KiB of LDS: five workgroups per CU)
 constexpr int kStageAhead = 128;  // longest list the staged product walks; also how far past its region it loads
 
@@ -219,18 +225,18 @@ __device__ __forceinline__ void group8_min_max(int v, int &mn, int &mx) {
 // load each (entry t + sub, clamped to the list's last entry), pass them through the wave's LDS slot, and
 // read all eight back (a broadcast read), so the memory path carries each entry once per neuron rather than
 // once per lane; the next block's entries are loaded while the current block's rows are in flight.
-#ifndef SDNN_BLOCKED_WAVES_PER_EU
-#define SDNN_BLOCKED_WAVES_PER_EU 1
-#endif
+// Waves per SIMD: five (98 VGPRs gave four; the LDS of five workgroups fits a CU): n 2^20, two layers, batch 1024 19.95
+// -> 19.66 ms per forward.  The pattern form would spill at five.
 // kStaged: the workgroup's lists sit in one region of the staged copy (`fan` then points to that copy); the
 // workgroup loads the whole region into LDS at once (16 bytes per lane, straight to LDS) and reads every
 // entry from there, so the only global loads of the loop are the rows.  Measured on the very wide layer: the
 // per-block entry loads from HBM sat on each block's critical path (94 -> 79 ms per layer without them).
 template <bool kPattern, bool kStaged>
-__global__ __launch_bounds__(kBWaves * 64) __attribute__((amdgpu_waves_per_eu(SDNN_BLOCKED_WAVES_PER_EU, 8))) void spmm_blocked_kernel(
+__global__ __launch_bounds__(kBWaves * 64) __attribute__((amdgpu_waves_per_eu(kPattern ? 4 : 5, 8))) void spmm_blocked_kernel(
     int64_t n, int64_t gpx, int64_t tiles, int64_t nchunk, int xcd_chunks, const BlockedSched *__restrict__ sched,
     const Edge *__restrict__ fan, const BlockedRegion *__restrict__ regions, const uint32_t *__restrict__ nzrows,
-    int64_t nz_words, const float *__restrict__ bias, double ymax, const float *__restrict__ yb, float *__restrict__ zb) {
+    int64_t nz_words, const float *__restrict__ bias, double ymax, const float *__restrict__ yb, float *__restrict__ zb,
+    uint8_t *__restrict__ counts) {
     __shared__ __align__(16) Edge ent[kStaged ? kStageCap : kBWaves * kBUnroll * 8];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = lane >> 3, sub = lane & 7;
@@ -296,6 +302,8 @@ __global__ __launch_bounds__(kBWaves * 64) __attribute__((amdgpu_waves_per_eu(SD
         // which reads zero without a memory access
         const uint32_t nrec = (uint32_t)n * (uint32_t)(kBW * 4);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)yc, (short)0, (int)nrec, 0x00020000);
+        // per group, a byte: (part of the neuron's run) * 16 + which of the lane's four outputs are nonzero
+        uint32_t nonzero = 0u;
         for (int gi = 0; gi < kBGroups; ++gi) {
             const BlockedSched cur = sp[8 * gi];
             int len = cur.len;
@@ -345,7 +353,26 @@ __global__ __launch_bounds__(kBWaves * 64) __attribute__((amdgpu_waves_per_eu(SD
                 out.z = (kPattern && (hit[2] & 0x7fffffffu) == 0u) ? 0.0f : activate(acc[2] + bd, ymax);
                 out.w = (kPattern && (hit[3] & 0x7fffffffu) == 0u) ? 0.0f : activate(acc[3] + bd, ymax);
                 *reinterpret_cast<float4 *>(zc + (int64_t)cur.j * kBW) = out;
+                nonzero |= ((uint32_t)(cur.j / kPackR % kRunParts) * 16u + (out.x != 0.0f ? 1u : 0u) +
+                            (out.y != 0.0f ? 2u : 0u) + (out.z != 0.0f ? 4u : 0u) + (out.w != 0.0f ? 8u : 0u))
+                           << (8 * gi);
             }
+        }
+        if (counts) {
+            // nonzeros per (part of the run, sample), in the lists' LDS once every wave is done with them
+            __syncthreads();
+            uint32_t *total = reinterpret_cast<uint32_t *>(ent);
+            total[threadIdx.x] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int gi = 0; gi < kBGroups; ++gi) {
+                const uint32_t byte = nonzero >> (8 * gi) & 0xffu;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if ((byte >> v) & 1u) atomicAdd(&total[(byte >> 4) * kBW + sub * 4 + v], 1u);
+            }
+            __syncthreads();
+            counts[(c * tiles + g) * kGroupCounts + threadIdx.x] = (uint8_t)total[threadIdx.x];
         }
         return;
     }
@@ -501,14 +528,16 @@ __global__ __launch_bounds__(kDensThreads) void densify_blocked_kernel(
     }
 }
 
-// Blocked activations -> CSR rows, in three steps.  Count: one wavefront per (chunk, part of kPackR
-// neurons) counts each sample's nonzeros in the part (lane = neuron, one ballot per sample).  Scan: per
+// Blocked activations -> CSR rows, in three steps.  Count: each sample's nonzeros in each part of kPackR neurons, from
+// the bytes the last product's workgroups left (their 64 neurons come from one run of 4096, so every workgroup counts
+// per part of its run and the bytes of a run's workgroups are added up here); a product that reads its lists from
+// memory leaves none, and then one wavefront per (chunk, part) counts (lane = neuron, one ballot per sample), which
+// reads all of Y_L again: 0.79 ms for 1024 samples of 2^20 neurons, against 0.03.  Scan: per
 // sample, the part counts become offsets within the row and the row total goes to cnt.  Pack: one
 // workgroup per (chunk, part) moves the part's 32 x kPackR values into LDS transposed, and each wave, for
 // each of its samples, compacts the survivors in ascending neuron order into its LDS area and then writes
 // the run at row_ptr[r] + offset with whole-wave stores aligned to 128-byte lines (a run of a few hundred
 // entries is written in whole lines but for its two ends).
-constexpr int kPackR = 512;
 constexpr int kTileLd = kBW + 1;  // LDS row pitch of a transposed 64 x 32 tile (conflict-free column reads)
 
 // Rows a .. a + 63 of chunk c (rows from a1 on read as zero) into v: lane l gets row a + l, all 32 samples.
@@ -559,6 +588,34 @@ __global__ __launch_bounds__(256) void blocked_count_kernel(int64_t n, int64_t b
         const int64_t r = c * kBW + s;
         if (lane == s && r < batch) pcnt[part * batch + r] = cnt[s];
     }
+}
+
+// pcnt[part][sample] from the product's bytes: a workgroup per (chunk, run), its waves a quarter of the run's workgroups
+// each; a lane adds four samples' bytes as two pairs of 16-bit sums (at most kPackR each).
+__global__ __launch_bounds__(256) void blocked_sum_counts_kernel(int64_t batch, int64_t tiles, int64_t runs, int64_t nparts,
+                                                                 const uint8_t *__restrict__ counts,
+                                                                 int32_t *__restrict__ pcnt) {
+    __shared__ uint32_t sums[4][2][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c = blockIdx.x / runs, run = blockIdx.x % runs;
+    const int64_t g0 = run * kRunTiles, g1 = min(tiles, g0 + kRunTiles);
+    uint32_t even = 0, odd = 0;
+#pragma unroll 4
+    for (int64_t g = g0 + wave; g < g1; g += 4) {
+        const uint32_t x = reinterpret_cast<const uint32_t *>(counts + (c * tiles + g) * kGroupCounts)[lane];
+        even += x & 0x00ff00ffu;
+        odd += (x >> 8) & 0x00ff00ffu;
+    }
+    sums[wave][0][lane] = even;
+    sums[wave][1][lane] = odd;
+    __syncthreads();
+    const int t = threadIdx.x;  // part t / 32 of the run, sample t % 32 of the chunk
+    const int64_t part = run * kRunParts + t / kBW, r = c * kBW + t % kBW;
+    if (part >= nparts || r >= batch) return;
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) total += (sums[w][t & 1][t / 4] >> (16 * ((t >> 1) & 1))) & 0xffffu;
+    pcnt[part * batch + r] = (int32_t)total;
 }
 
 // Per sample: part counts -> exclusive offsets within the row (in place); row totals -> cnt.  A workgroup takes 64
@@ -757,7 +814,7 @@ hipError_t launch_blocked_stage(int64_t n, int64_t nnz, const Edge *fan, Blocked
 
 hipError_t launch_spmm_blocked(int64_t n, int64_t batch, const BlockedSched *sched, const Edge *fan,
                                const BlockedRegion *regions, const uint32_t *nzrows, const float *bias, double ymax,
-                               int pattern, const float *yb, float *zb, hipStream_t s) {
+                               int pattern, const float *yb, float *zb, uint8_t *counts, hipStream_t s) {
     if (n == 0 || batch == 0) return hipSuccess;
     if (n > (1 << 24)) return hipErrorInvalidValue;  // 32-bit row offsets within a chunk
     const int64_t nchunks = blocked_chunks(batch);
@@ -781,15 +838,16 @@ hipError_t launch_spmm_blocked(int64_t n, int64_t batch, const BlockedSched *sch
         float *z0 = zb + c0 * n * kBW;
         const int64_t words = blocked_nz_words(n);
         const uint32_t *nz0 = (regions && nzrows) ? nzrows + c0 * words : nullptr;
+        uint8_t *c0p = counts && regions ? counts + c0 * groups * kGroupCounts : nullptr;
         if (regions) {
             if (pattern)
-                spmm_blocked_kernel<true, true><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, regions, nz0, words, bias, ymax, y0, z0);
+                spmm_blocked_kernel<true, true><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, regions, nz0, words, bias, ymax, y0, z0, c0p);
             else
-                spmm_blocked_kernel<false, true><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, regions, nz0, words, bias, ymax, y0, z0);
+                spmm_blocked_kernel<false, true><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, regions, nz0, words, bias, ymax, y0, z0, c0p);
         } else if (pattern) {
-            spmm_blocked_kernel<true, false><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, nullptr, nullptr, 0, bias, ymax, y0, z0);
+            spmm_blocked_kernel<true, false><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, nullptr, nullptr, 0, bias, ymax, y0, z0, nullptr);
         } else {
-            spmm_blocked_kernel<false, false><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, nullptr, nullptr, 0, bias, ymax, y0, z0);
+            spmm_blocked_kernel<false, false><<<nb, kBWaves * 64, 0, s>>>(n, gpx, groups, nc, xcd_chunks, sched, fan, nullptr, nullptr, 0, bias, ymax, y0, z0, nullptr);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -814,7 +872,7 @@ hipError_t launch_densify_blocked(int64_t n, int64_t batch, const int64_t *in_ro
     return hipGetLastError();
 }
 
-hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int32_t *pcnt, int32_t *cnt,
+hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, const uint8_t *counts, int32_t *pcnt, int32_t *cnt,
                                  int64_t *row_ptr, int64_t *scan_tmp, const HostReport &report, int32_t *out_col,
                                  float *out_val, hipStream_t s) {
     if (batch == 0) return hipSuccess;
@@ -822,7 +880,12 @@ hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int3
     const int64_t waves = blocked_chunks(batch) * nparts;
     const int64_t blocks = (waves + 3) / 4;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    blocked_count_kernel<<<(unsigned)blocks, 256, 0, s>>>(n, batch, nparts, yb, pcnt);
+    const int64_t runs = (n + kSortSeg - 1) / kSortSeg;
+    if (counts)
+        blocked_sum_counts_kernel<<<(unsigned)(blocked_chunks(batch) * runs), 256, 0, s>>>(batch, (n + kBTile - 1) / kBTile,
+                                                                                           runs, nparts, counts, pcnt);
+    else
+        blocked_count_kernel<<<(unsigned)blocks, 256, 0, s>>>(n, batch, nparts, yb, pcnt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     blocked_scan_kernel<<<(unsigned)((batch + 63) / 64), kScanWaves * 64, 0, s>>>(batch, nparts, pcnt, cnt);

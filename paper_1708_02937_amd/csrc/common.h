@@ -261,10 +261,12 @@ hipError_t launch_blocked_stage(int64_t n, int64_t nnz, const Edge *fan, Blocked
 // regions: the staged lists (null when a region exceeds blocked_stage_cap(): entries come from fan instead).
 // nzrows (with regions only, may be null): per chunk a map of blocked_nz_words(n) words, bit i set when
 // input row i holds a nonzero; the product then reads no row that is zero in its chunk.
+// counts (with regions only, may be null; 256 bytes per 64 neurons and chunk: n * batch / 8 bytes and the rounding)
+// receives what launch_blocked_to_csr needs to know of the output's nonzeros.
 int64_t blocked_nz_words(int64_t n);
 hipError_t launch_spmm_blocked(int64_t n, int64_t batch, const BlockedSched *sched, const Edge *fan,
                                const BlockedRegion *regions, const uint32_t *nzrows, const float *bias, double ymax,
-                               int pattern, const float *yb, float *zb, hipStream_t s);
+                               int pattern, const float *yb, float *zb, uint8_t *counts, hipStream_t s);
 // sparse rows (caller CSR, or slot rows with counts) -> blocked; every element is written, except that when
 // nzrows is not null the rows of a chunk that hold no nonzero are not stored (only a product given the same map,
 // which reads no such row, may consume the result), and the nonzero-row map of every chunk
@@ -273,7 +275,8 @@ hipError_t launch_densify_blocked(int64_t n, int64_t batch, const int64_t *in_ro
                                   const int32_t *in_col, const float *in_val, float *yb, uint32_t *nzrows, uint32_t *err,
                                   hipStream_t s);
 // blocked -> CSR: pcnt holds blocked_pack_elems int32, cnt batch int32, row_ptr batch + 1
-hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, int32_t *pcnt, int32_t *cnt,
+// counts: of the product that wrote yb, or null (then yb is read for them)
+hipError_t launch_blocked_to_csr(int64_t n, int64_t batch, const float *yb, const uint8_t *counts, int32_t *pcnt, int32_t *cnt,
                                  int64_t *row_ptr, int64_t *scan_tmp, const HostReport &report, int32_t *out_col,
                                  float *out_val, hipStream_t s);
 // batch-major (row pitch ld) <-> blocked
