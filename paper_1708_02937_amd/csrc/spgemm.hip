@@ -42,7 +42,7 @@ constexpr int kBitWords = kTile / 32;
 
 // One stored entry of the sample with the extent of its fan-out row segment (wave-private LDS staging).
 struct RowRef {
-    double y;
+    float y;
     int32_t start;
     int32_t len;
 };
@@ -536,21 +536,24 @@ __global__ __launch_bounds__(kThreads) void spgemm_row_kernel(
                         }
                     }
                 } else {
-                    // each wave takes 64 stored entries of the sample at once (one per lane, coalesced),
-                    // gathers the extents of their fan-out row segments and parks (y, start, length) in
+                    // each wave takes up to 64 stored entries of the sample at once (one per lane, coalesced; fewer
+                    // when the sample has less than 64 per wave, so that every wave has some: n 7624, 130 entries
+                    // of 32 per sample, batch 3594 268 -> 160 us), gathers the extents of their fan-out row segments and parks (y, start, length) in
                     // its own LDS area; then each half-wave reads one segment with 32 lanes (a coalesced
                     // load), four segments per half in flight, and adds the exact products
                     RowRef *my = refs + wave * 64;
-                    for (int64_t base = (int64_t)wave * 64; base < ylen; base += kThreads) {
+                    const int64_t even = (ylen + kWaves - 1) / kWaves;
+                    const int take = lane_segments || even > 56 ? 64 : (int)((even + 7) & ~7);
+                    for (int64_t base = (int64_t)wave * take; base < ylen; base += kWaves * take) {
                         const int64_t t = base + lane;
                         RowRef ref;
-                        ref.y = 0.0;
+                        ref.y = 0.0f;
                         ref.start = 0;
                         ref.len = 0;
-                        if (t < ylen) {
+                        if (t < ylen && lane < take) {
                             const int32_t i = in_col[yb + t];
                             if (i >= 0 && i < n) {
-                                ref.y = (double)in_val[yb + t];
+                                ref.y = in_val[yb + t];
                                 const int64_t rb = w_ptr[i];
                                 if (w_seg) {
                                     const int32_t *sg = w_seg + (int64_t)i * (nwin + 1) + win;
@@ -585,15 +588,15 @@ __global__ __launch_bounds__(kThreads) void spgemm_row_kernel(
                                 for (int u = 0; u < 8; ++u) {
                                     ok[u] = ed[u].idx >= c0 && ed[u].idx < c1;
                                     col[u] = ed[u].idx - (int)c0;
-                                    v[u] = ref.y * (double)ed[u].w;
+                                    v[u] = (double)ref.y * (double)ed[u].w;
                                     mine_any |= ok[u];
                                 }
-                                add_products(acc, bits, col, v, ok, sparse && ref.y != 0.0, cross, zero_below);
+                                add_products(acc, bits, col, v, ok, sparse && ref.y != 0.0f, cross, zero_below);
                             }
                             continue;
                         }
                         my[lane] = ref;
-                        const int nref = (int)((ylen - base) < 64 ? (ylen - base) : 64);
+                        const int nref = (int)((ylen - base) < take ? (ylen - base) : take);
                         for (int rr0 = 0; rr0 < nref; rr0 += 8) {
                             RowRef rr[4];
 #pragma unroll
@@ -621,7 +624,7 @@ __global__ __launch_bounds__(kThreads) void spgemm_row_kernel(
                                 for (int p = 0; p < 4; ++p) {
                                     ok[p] = ed[p].idx >= c0 && ed[p].idx < c1;
                                     col[p] = ed[p].idx - (int)c0;
-                                    v[p] = rr[p].y * (double)ed[p].w;
+                                    v[p] = (double)rr[p].y * (double)ed[p].w;
                                     mine_any |= ok[p];
                                 }
                                 if (cross) {
@@ -631,7 +634,7 @@ __global__ __launch_bounds__(kThreads) void spgemm_row_kernel(
                                     for (int p = 0; p < 4; ++p)
                                         if (ok[p]) {
                                             atomicAdd(&acc[acc_pos(col[p])], v[p]);
-                                            if (sparse && rr[p].y != 0.0) atomicOr(&bits[col[p] >> 5], 1u << (col[p] & 31));
+                                            if (sparse && rr[p].y != 0.0f) atomicOr(&bits[col[p] >> 5], 1u << (col[p] & 31));
                                         }
                                 }
                             }

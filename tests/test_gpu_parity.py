@@ -1133,3 +1133,10 @@ def test_blocked_densify_checks_every_column(sd, n, batch, rows, bad):
     got = [x.cpu().numpy() for x in net.forward_csr(rp, c, v)]
     net.free()
     parity.compare(p, tuple(got))
+
+
+@pytest.mark.parametrize("n,fan,biases", [(6000, (30, 50), (-1.0, -2.0)), (9000, (30, 50), (0.0, -1.0)), (6000, (4, 24), (-1.0,))])
+def test_spgemm_sample_lengths(sd, n, fan, biases):
+    """Samples of 1 to 1100 entries on the workgroup instances, long fan-out rows (half-wave segments, the entries shared
+    out evenly over the waves in groups of 8 to 64) and short ones, one accumulator window; bit for bit."""
+    test_spgemm_crossing_marks(sd, n, fan, (1, 1100), biases, 400)
