@@ -227,9 +227,10 @@ sdnn_status sdnn_forward_dense(sdnn_net net, int32_t k0, int32_t k1, int64_t bat
  * harnesses that forbid allocation): sdnn_forward_dense without a workspace argument.  Its workspace (the two
  * activation buffers and the dense arm's partial sums) is a fixed device array of the library, one per
  * GPU, sdnn_noalloc_scratch_bytes() bytes (64 MiB), held from the first sdnn_net_create on that GPU until
- * the process ends.  The call itself allocates and frees nothing.  Layers whose workspace
- * (sdnn_workspace_size(net, batch, 0), its rounding of the batch to a multiple of four aside) exceeds that size are
- * refused with UNSUPPORTED.  Every call on one
+ * the process ends.  The call itself allocates and frees nothing.  A batch is accepted when two activation
+ * buffers of n x batch floats and the fp64 sums of every K split of a dense arm fit the array, and refused
+ * with UNSUPPORTED before anything is launched otherwise (the padding that sdnn_workspace_size counts in
+ * decides nothing: a dense arm runs a batch whose padded buffers do not fit part by part).  Every call on one
  * GPU shares the array, which keeps the last call's contents: calls that overlap on one GPU (other host
  * threads, other nets or streams without ordering between them) race and give undefined results.  Same
  * arguments, result and errors as sdnn_forward_dense otherwise.

@@ -86,8 +86,8 @@ struct Layer {
     bool dense_ready = false, dense32_ready = false;  // the dense copies hold the current W_k
 };
 
+using sdnn::align_up;
 constexpr size_t kAlign = 256;
-inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // ---------------------------------------------------------------------------------------- net arena
 // All device memory a net keeps lives in one caller-owned arena, laid out once at creation from n, L, the
@@ -221,26 +221,10 @@ CsrWs carve_csr(void *base, int64_t n, int64_t batch) {
 
 constexpr int64_t kMaxScan = 16777216;  // longest array the device prefix sum handles (fan-in pointers, row pointers)
 
-// bytes of one neuron-major activation buffer at row pitch ld
-size_t act_bytes(int64_t n, int64_t ld) { return align_up((size_t)n * (size_t)ld * sizeof(float)); }
-
-// two activation buffers of a dense arm, in its operand layout, and its split-K partial sums (small batches only)
-size_t arm_act_bytes(int64_t n, int64_t batch) { return align_up(sdnn::gemm_act_elems(n, batch) * sizeof(float)); }
-size_t arm_ws_bytes(int64_t n, int64_t batch, int num_cu) {
-    return 2 * arm_act_bytes(n, batch) + align_up(sdnn::gemm_partial_bytes(n, batch, num_cu));
-}
-
 // a dense-Y call's workspace: two neuron-major activation buffers, or, for a net with dense copies, what the arms need
 size_t dense_ws_bytes(int64_t n, int64_t batch, int32_t dense_flags, int num_cu) {
-    const size_t sparse = 2 * act_bytes(n, sdnn::act_ld(n, batch));
-    return dense_flags ? std::max(sparse, arm_ws_bytes(n, batch, num_cu)) : sparse;
-}
-
-// What decides whether the fixed scratch array takes a batch: two buffers of n x batch and fp64 sums of every K split.
-size_t noalloc_bytes(int64_t n, int64_t batch, int num_cu) {
-    const int sp = sdnn::gemm_splits(n, batch, num_cu);
-    const size_t sums = sp > 1 ? (size_t)sp * (size_t)n * (size_t)batch * sizeof(double) : 0;
-    return 2 * act_bytes(n, sdnn::act_ld_tight(n, batch)) + align_up(sums);
+    const size_t sparse = 2 * sdnn::act_bytes(n, sdnn::act_ld(n, batch));
+    return dense_flags ? std::max(sparse, sdnn::arm_ws_bytes(n, batch, sdnn::gemm_splits(n, batch, num_cu))) : sparse;
 }
 
 // Workspace of sdnn_forward_dense_noalloc: a fixed device array, one copy per GPU, held until the process
@@ -718,6 +702,39 @@ static sdnn_status run_resident(sdnn_net net, int32_t k0, int32_t k1, int64_t ba
     return SDNN_OK;
 }
 
+// Layers [k0, k1) on a dense arm, activations in the matrix cores' operand layout throughout; ws holds
+// arm_ws_bytes(n, batch, splits) bytes.
+static sdnn_status run_arm(sdnn_net net, int32_t k0, int32_t k1, int64_t batch, const float *Y_in, float *Y_out, void *ws,
+                           int32_t arm, int splits) {
+    const int64_t n = net->n;
+    hipStream_t s = net->stream;
+    const bool f64 = arm == SDNN_ARM_DENSE;
+    const size_t bytes = sdnn::arm_act_bytes(n, batch);
+    float *act[2] = {(float *)ws, (float *)((char *)ws + bytes)};
+    void *partial = (char *)ws + 2 * bytes;
+    int pr = -1;
+    SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
+    SDNN_HIP(sdnn::launch_to_quads(n, batch, f64, Y_in, act[0], s));
+    SDNN_HIP(prof_end(net, pr));
+    int cur = 0;
+    for (int32_t k = k0; k < k1; ++k) {
+        const Layer &l = net->layers[(size_t)k];
+        SDNN_HIP(prof_begin(net, k, f64 ? sdnn::kKernDenseGemm : sdnn::kKernDenseGemm32, &pr));
+        if (f64)
+            SDNN_HIP(sdnn::launch_gemm_dense_layer(n, batch, l.dense_wt, l.bias, net->ymax, act[cur], act[cur ^ 1],
+                                                   (double *)partial, splits, s));
+        else
+            SDNN_HIP(sdnn::launch_gemm32_dense_layer(n, batch, l.dense_wt32, l.bias, net->ymax, act[cur], act[cur ^ 1],
+                                                     (float *)partial, splits, s));
+        SDNN_HIP(prof_end(net, pr));
+        cur ^= 1;
+    }
+    SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
+    SDNN_HIP(sdnn::launch_from_quads(n, batch, f64, act[cur], Y_out, s));
+    SDNN_HIP(prof_end(net, pr));
+    return SDNN_OK;
+}
+
 static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int64_t batch, const float *Y_in,
                                       float *Y_out, void *ws, int64_t ws_bytes, int32_t arm, bool static_ws) {
     if (!net) return fail(SDNN_ERR_INVALID_OBJECT, "net is NULL");
@@ -745,24 +762,11 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         if (!slot || !slot->ptr)
             return fail(SDNN_ERR_DEVICE, std::string("scratch array of the allocation-free entry point unavailable: ") +
                                              hipGetErrorString(slot ? slot->err : hipErrorInvalidDevice));
-        if (noalloc_bytes(n, batch, net->num_cu) > kScratchBytes)
+        if (sdnn::noalloc_bytes(n, batch, net->num_cu) > kScratchBytes)
             return fail(SDNN_ERR_UNSUPPORTED,
-                        "batch x n needs " + std::to_string(noalloc_bytes(n, batch, net->num_cu)) +
+                        "batch x n needs " + std::to_string(sdnn::noalloc_bytes(n, batch, net->num_cu)) +
                             " bytes of scratch; the allocation-free entry point holds " + std::to_string(kScratchBytes));
-        if (2 * act_bytes(n, ld) > kScratchBytes) ld = sdnn::act_ld_tight(n, batch);
-        if (arm != SDNN_ARM_SPARSE && batch > 1 && arm_ws_bytes(n, batch, net->num_cu) > kScratchBytes) {
-            // the padding of the arms' layout does not fit at this size: two halves, in the order in which neither
-            // overwrites rows of Y_in that the other still reads
-            const int64_t half = batch > 64 ? (batch / 2 + 63) / 64 * 64 : (batch + 1) / 2;
-            const bool up = (uintptr_t)Y_out > (uintptr_t)Y_in;
-            for (int part = 0; part < 2; ++part) {
-                const bool first = (part == 0) != up;
-                const int64_t r0 = first ? 0 : half, rows = first ? half : batch - half;
-                st = forward_dense_impl(net, k0, k1, rows, Y_in + r0 * n, Y_out + r0 * n, nullptr, 0, arm, true);
-                if (st != SDNN_OK) return st;
-            }
-            return SDNN_OK;
-        }
+        if (2 * sdnn::act_bytes(n, ld) > kScratchBytes) ld = sdnn::act_ld_tight(n, batch);
         ws = slot->ptr;
         ws_bytes = (int64_t)kScratchBytes;
     }
@@ -775,34 +779,20 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             return fail(SDNN_ERR_INVALID_OBJECT, "dense arm requested before sdnn_net_build_dense (or without its copy "
                                                  "in the arena)");
     }
-    int pr = -1;
     if (arm != SDNN_ARM_SPARSE) {
-        // a dense arm: activations in the matrix cores' operand layout throughout
-        const bool f64 = arm == SDNN_ARM_DENSE;
-        float *act[2] = {(float *)ws, (float *)((char *)ws + arm_act_bytes(n, batch))};
-        void *partial = (char *)ws + 2 * arm_act_bytes(n, batch);
-        SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
-        SDNN_HIP(sdnn::launch_to_quads(n, batch, f64, Y_in, act[0], s));
-        SDNN_HIP(prof_end(net, pr));
-        int ca = 0;
-        for (int32_t k = k0; k < k1; ++k) {
-            const Layer &l = net->layers[(size_t)k];
-            SDNN_HIP(prof_begin(net, k, f64 ? sdnn::kKernDenseGemm : sdnn::kKernDenseGemm32, &pr));
-            if (f64)
-                SDNN_HIP(sdnn::launch_gemm_dense_layer(n, batch, l.dense_wt, l.bias, net->ymax, act[ca], act[ca ^ 1],
-                                                       (double *)partial, net->num_cu, s));
-            else
-                SDNN_HIP(sdnn::launch_gemm32_dense_layer(n, batch, l.dense_wt32, l.bias, net->ymax, act[ca], act[ca ^ 1],
-                                                         (float *)partial, net->num_cu, s));
-            SDNN_HIP(prof_end(net, pr));
-            ca ^= 1;
+        const sdnn::ArmPlan plan = sdnn::plan_arm(n, batch, net->num_cu, (size_t)ws_bytes);
+        if (plan.rows == 0) return fail(SDNN_ERR_UNSUPPORTED, "one sample does not fit the scratch array");
+        // parts in the order in which none overwrites rows of Y_in that a later one reads
+        const int64_t parts = (batch + plan.rows - 1) / plan.rows;
+        for (int64_t i = 0; i < parts; ++i) {
+            const int64_t r0 = ((uintptr_t)Y_out > (uintptr_t)Y_in ? parts - 1 - i : i) * plan.rows;
+            st = run_arm(net, k0, k1, std::min(plan.rows, batch - r0), Y_in + r0 * n, Y_out + r0 * n, ws, arm, plan.splits);
+            if (st != SDNN_OK) return st;
         }
-        SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
-        SDNN_HIP(sdnn::launch_from_quads(n, batch, f64, act[ca], Y_out, s));
-        SDNN_HIP(prof_end(net, pr));
         return SDNN_OK;
     }
-    float *buf[2] = {(float *)ws, (float *)((char *)ws + act_bytes(n, ld))};
+    int pr = -1;
+    float *buf[2] = {(float *)ws, (float *)((char *)ws + sdnn::act_bytes(n, ld))};
     if (use_blocked(net, k0, k1, batch)) {
         // the sample-blocked layout (each buffer holds n x ld >= n x round32(batch) floats)
         SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
@@ -1126,7 +1116,7 @@ sdnn_status sdnn_mxm_dense(sdnn_net net, int32_t k, int32_t semiring, int64_t ba
     }
     const int64_t ld = sdnn::act_ld(n, batch);
     float *yt = (float *)ws;
-    float *zt = (float *)((char *)ws + act_bytes(n, ld));
+    float *zt = (float *)((char *)ws + sdnn::act_bytes(n, ld));
     SDNN_HIP(sdnn::launch_transpose(Y, n, yt, ld, batch, n, s));  // batch x n -> n x batch
     SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, yt, zt, s));
     SDNN_HIP(sdnn::launch_transpose(zt, ld, Z, n, n, batch, s));  // n x batch -> batch x n

@@ -6,6 +6,8 @@
 
 #include <atomic>
 
+#include "sizes.h"
+
 namespace sdnn {
 
 // A weight entry packed for one 64-bit load: the other end of the edge and its fp32 value.
@@ -93,19 +95,6 @@ hipError_t launch_fanin_lists(int64_t n, int64_t nnz, const int64_t *row_ptr, co
 hipError_t launch_max_segment(int64_t n, const int64_t *ptr, int32_t *out, hipStream_t s);
 hipError_t launch_pack_edges(int64_t nnz, const int32_t *col, const float *val, Edge *out, hipStream_t s);
 
-// Row pitch (floats) of the neuron-major activation buffers Y^T (n rows of `batch` samples).  Lines taken one
-// per row at a power-of-two byte pitch fall into a fraction of an XCD's L2 sets (measured on MI355X: at a
-// 16 KiB pitch a 1 MiB working set already misses about half the time, at 16 KiB + 256 B a 3 MiB one stays
-// resident), so for wide layers (n > 4096) of 256 samples or more the pitch is an odd multiple of 64 floats
-// (256 bytes).  At n = 4096, batch 1024 the padding measured 1-3% slower per layer, so narrower layers and
-// smaller batches keep the dense pitch, rounded up to whole 16-byte loads.
-inline int64_t act_ld(int64_t n, int64_t batch) {
-    return (n <= 4096 || batch < 256) ? (batch + 3) / 4 * 4 : (((batch + 63) / 64) | 1) * 64;
-}
-// The same without the rounding, for a workspace that has no room for it.
-inline int64_t act_ld_tight(int64_t n, int64_t batch) {
-    return (n <= 4096 || batch < 256) ? batch : act_ld(n, batch);
-}
 // Samples the neuron-major products compute: the batch rounded up to a multiple of four when the pitch has room.
 // The samples past the batch hold whatever the buffer held and are not copied out; a sample depends on no other.
 // (An odd batch otherwise gathers one column per lane: n 9001, 60 entries per neuron, batch 333, four layers took 318 us
@@ -173,20 +162,16 @@ hipError_t launch_semiring_resident(int semiring, const ResidentLayer &layer, in
                                     const float *y, float *z, hipStream_t s);
 
 // gemm.hip: the dense-W arms.  Weights and activations are in the matrix-core operand layout (K padded to 32).
-size_t gemm_weight_elems(int64_t n);                // values of one dense copy
-size_t gemm_act_elems(int64_t n, int64_t batch);    // floats of one activation buffer
-int gemm_splits(int64_t n, int64_t batch, int num_cu);
-size_t gemm_partial_bytes(int64_t n, int64_t batch, int num_cu);
 hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s);
 hipError_t launch_dense32_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, float *wt, hipStream_t s);
 // batch-major <-> the arms' activation layout (f64: of the fp64 arm)
 hipError_t launch_to_quads(int64_t n, int64_t batch, bool f64, const float *y, float *yq, hipStream_t s);
 hipError_t launch_from_quads(int64_t n, int64_t batch, bool f64, const float *yq, float *y, hipStream_t s);
-// partial: gemm_partial_bytes(n, batch, num_cu) bytes of scratch (unused when that is 0; the fp32 arm's as fp32).
+// partial: the sums of at most `splits` K splits (unused when that is 1).
 hipError_t launch_gemm_dense_layer(int64_t n, int64_t batch, const double *wt, const float *bias, double ymax,
-                                   const float *yq, float *zq, double *partial, int num_cu, hipStream_t s);
+                                   const float *yq, float *zq, double *partial, int splits, hipStream_t s);
 hipError_t launch_gemm32_dense_layer(int64_t n, int64_t batch, const float *wt, const float *bias, double ymax,
-                                     const float *yq, float *zq, float *partial, int num_cu, hipStream_t s);
+                                     const float *yq, float *zq, float *partial, int splits, hipStream_t s);
 
 // spgemm.hip
 size_t spgemm_lds_bytes(int64_t n);

@@ -44,12 +44,8 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = 128, BN = 64, BK = 16;
+constexpr int BM = kGemmM, BN = kGemmN, BK = kGemmK, kKPad = kGemmKPad;
 constexpr int kThreads = 512;  // 8 waves of 32 x 32 outputs
-constexpr int kKPad = 32;
-
-int64_t k_blocks(int64_t n) { return (n + kKPad - 1) / kKPad * (kKPad / BK); }
-int64_t m_pitch(int64_t n) { return (n + BM - 1) / BM * BM; }
 
 // Neuron of value v of lane group q in a block of 16.
 template <typename T>
@@ -347,24 +343,23 @@ template <typename T>
 hipError_t launch_weights(int64_t n, const int64_t *fan_ptr, const Edge *fan, T *wt, hipStream_t s) {
     hipError_t e = hipMemsetAsync(wt, 0, gemm_weight_elems(n) * sizeof(T), s);
     if (e != hipSuccess) return e;
-    dense_weights_kernel<T><<<(unsigned)n, 256, 0, s>>>(n, m_pitch(n), fan_ptr, fan, wt);
+    dense_weights_kernel<T><<<(unsigned)n, 256, 0, s>>>(n, gemm_m_pitch(n), fan_ptr, fan, wt);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_gemm(int64_t n, int64_t batch, const T *wt, const float *bias, double ymax, const float *yq, float *zq,
-                       T *partial, int num_cu, hipStream_t s) {
+                       T *partial, int splits, hipStream_t s) {
     if (n == 0 || batch == 0) return hipSuccess;
-    const int64_t gx = (n + BM - 1) / BM, gy = (batch + BN - 1) / BN, blocks = k_blocks(n);
+    const int64_t gx = (n + BM - 1) / BM, gy = (batch + BN - 1) / BN, blocks = gemm_k_blocks(n);
     if (gx > 0x7fffffffLL || gy > 65535) return hipErrorInvalidValue;
-    int sp = gemm_splits(n, batch, num_cu);
     // split length in whole K steps; the last split may be shorter, none is empty
     const int64_t steps = blocks / (kKPad / BK);
-    const int64_t kc = (steps + sp - 1) / sp * (kKPad / BK);
-    sp = (int)((blocks + kc - 1) / kc);
+    const int64_t kc = (steps + splits - 1) / splits * (kKPad / BK);
+    const int sp = (int)((blocks + kc - 1) / kc);
     T *part = sp > 1 ? partial : nullptr;
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)sp);
-    gemm_dense_layer_kernel<T><<<grid, kThreads, 0, s>>>(n, batch, m_pitch(n), blocks, kc,
+    gemm_dense_layer_kernel<T><<<grid, kThreads, 0, s>>>(n, batch, gemm_m_pitch(n), blocks, kc,
                                         reinterpret_cast<const typename Arm<T>::Unit *>(wt),
                                         reinterpret_cast<const floatx4 *>(yq), bias, ymax, reinterpret_cast<float4 *>(zq),
                                         part);
@@ -377,26 +372,6 @@ hipError_t launch_gemm(int64_t n, int64_t batch, const T *wt, const float *bias,
 
 }  // namespace
 
-size_t gemm_weight_elems(int64_t n) { return (size_t)(k_blocks(n) * BK) * (size_t)m_pitch(n); }
-
-size_t gemm_act_elems(int64_t n, int64_t batch) { return (size_t)(k_blocks(n) * BK) * (size_t)batch; }
-
-// K splits for an n x n layer on `batch` samples: enough workgroups for two per CU, at least 8 K steps each.
-int gemm_splits(int64_t n, int64_t batch, int num_cu) {
-    const int64_t tiles = ((n + BM - 1) / BM) * ((batch + BN - 1) / BN);
-    if (tiles == 0 || tiles >= 2 * (int64_t)num_cu) return 1;
-    int64_t sp = (2 * (int64_t)num_cu + tiles - 1) / tiles;
-    const int64_t most = n / (8 * BK);
-    if (sp > most) sp = most;
-    if (sp > 64) sp = 64;
-    return sp < 1 ? 1 : (int)sp;
-}
-
-size_t gemm_partial_bytes(int64_t n, int64_t batch, int num_cu) {
-    const int sp = gemm_splits(n, batch, num_cu);
-    return sp > 1 ? (size_t)sp * gemm_act_elems(n, batch) * sizeof(double) : 0;
-}
-
 hipError_t launch_dense_from_fanin(int64_t n, const int64_t *fan_ptr, const Edge *fan, double *wt, hipStream_t s) {
     return launch_weights<double>(n, fan_ptr, fan, wt, s);
 }
@@ -405,19 +380,19 @@ hipError_t launch_dense32_from_fanin(int64_t n, const int64_t *fan_ptr, const Ed
 }
 
 hipError_t launch_gemm_dense_layer(int64_t n, int64_t batch, const double *wt, const float *bias, double ymax,
-                                   const float *yq, float *zq, double *partial, int num_cu, hipStream_t s) {
-    return launch_gemm<double>(n, batch, wt, bias, ymax, yq, zq, partial, num_cu, s);
+                                   const float *yq, float *zq, double *partial, int splits, hipStream_t s) {
+    return launch_gemm<double>(n, batch, wt, bias, ymax, yq, zq, partial, splits, s);
 }
 hipError_t launch_gemm32_dense_layer(int64_t n, int64_t batch, const float *wt, const float *bias, double ymax,
-                                     const float *yq, float *zq, float *partial, int num_cu, hipStream_t s) {
-    return launch_gemm<float>(n, batch, wt, bias, ymax, yq, zq, partial, num_cu, s);
+                                     const float *yq, float *zq, float *partial, int splits, hipStream_t s) {
+    return launch_gemm<float>(n, batch, wt, bias, ymax, yq, zq, partial, splits, s);
 }
 
 namespace {
 
 template <typename T>
 hipError_t launch_quads(int64_t n, int64_t batch, bool to, const float *in, float *out, hipStream_t s) {
-    const int64_t R = n * batch <= (int64_t(1) << 20) ? 32 : 64, cols = to ? k_blocks(n) * BK : n;
+    const int64_t R = n * batch <= (int64_t(1) << 20) ? 32 : 64, cols = to ? gemm_k_blocks(n) * BK : n;
     const dim3 grid((unsigned)((batch + R - 1) / R), (unsigned)((cols + R - 1) / R));
     if ((cols + R - 1) / R > 65535) return hipErrorInvalidValue;
     if (to && R == 32)

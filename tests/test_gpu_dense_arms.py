@@ -54,3 +54,30 @@ def test_scratch_array_in_halves(arm):
     sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, y, y, code)
     assert torch.equal(y, want)
     net.free()
+
+
+@pytest.mark.parametrize("arm", ["f64", "f32"])
+@pytest.mark.parametrize("n,batch", [(639, 13108), (3835, 2185)])
+def test_scratch_array_parts_keep_the_splits(arm, n, batch):
+    """Batches of which a half alone has few enough tiles to ask for K splits the whole batch has none of: the parts run
+    at the whole batch's splits, so the result is that of the workspace entry point bit for bit; out of place, in place,
+    and with the output shifted by a few rows over the input in either direction."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = tiny_random(3, n, 1, 4, w_density=0.01, dense_input=True)
+    code, flag = {"f64": (sd.SDNN_ARM_DENSE, 1), "f32": (sd.SDNN_ARM_DENSE_F32, 2)}[arm]
+    net = sd.net_from_problem(p, dense=flag)
+    y = torch.from_numpy(np.random.default_rng(2).random((batch, n), dtype=np.float32)).cuda()
+    want = net.forward_dense(y, arm=code)
+    for shift in (None, 0, 5, -5):
+        print("[case] scratch parts", arm, n, batch, shift, flush=True)
+        room = torch.empty((batch + 5, n), device="cuda")
+        lo = 5 if shift is not None and shift < 0 else 0  # where the input starts
+        src = room[lo:lo + batch]
+        src.copy_(y)
+        out = torch.empty_like(y) if shift is None else room[lo + shift:lo + shift + batch]
+        sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, src, out, code)
+        assert torch.equal(out, want)
+    net.free()
