@@ -220,11 +220,11 @@ struct Slice {
     float4 w[kAhead];
 };
 
-// grid: (sample groups, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
+// grid: (sample groups from sample `base` on, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
 // part (a single layer then) every part's workgroup reads all input rows and writes its own neurons.
 template <int V, class Op>
 __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs args, int layers, int n, int64_t batch,
-                                                                  int nslices, int runs, double ymax,
+                                                                  int64_t base, int nslices, int runs, double ymax,
                                                                   ResidentIo io) {
     using Row = typename RowOf<V>::T;
     extern __shared__ __align__(16) char resident_lds[];
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
     Row *dst = src + (n + 1);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t r0 = (int64_t)blockIdx.x * V;
+    const int64_t r0 = base + (int64_t)blockIdx.x * V;
     const int rows = (int)(batch - r0 < V ? batch - r0 : V);
     const int run0 = blockIdx.y * runs;
     const int run1 = min(run0 + runs, (nslices + kRunSlices - 1) / kRunSlices);
@@ -479,10 +479,14 @@ hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t bat
     const hipError_t e = raise_lds_limit((const void *)spmm_resident_kernel<V, Op>, kMaxLds, attr_devices);
     if (e != hipSuccess) return e;
     const int64_t groups = (batch + V - 1) / V;
-    if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-    spmm_resident_kernel<V, Op><<<dim3((unsigned)groups, (unsigned)parts), kRThreads, lds, s>>>(
-        args, layers, (int)n, batch, (int)((n + 63) / 64), per, ymax, io);
-    return hipGetLastError();
+    const int64_t seg = (int64_t(1) << 21) / parts;  // groups per launch: fewer than 2^32 work-items
+    for (int64_t g0 = 0; g0 < groups; g0 += seg) {
+        spmm_resident_kernel<V, Op><<<dim3((unsigned)std::min(seg, groups - g0), (unsigned)parts), kRThreads, lds, s>>>(
+            args, layers, (int)n, batch, g0 * V, (int)((n + 63) / 64), per, ymax, io);
+        const hipError_t el = hipGetLastError();
+        if (el != hipSuccess) return el;
+    }
+    return hipSuccess;
 }
 
 template <class Op>
