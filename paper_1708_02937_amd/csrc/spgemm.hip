@@ -1182,12 +1182,12 @@ __global__ __launch_bounds__(256) void densify_kernel(int64_t n, int64_t batch, 
 constexpr int kSlotThreads = 1024;
 constexpr int kSlotWaves = kSlotThreads / 64;
 
-__global__ __launch_bounds__(kSlotThreads) void dense_to_rows_kernel(int64_t n, const float *__restrict__ y,
+__global__ __launch_bounds__(kSlotThreads) void dense_to_rows_kernel(int64_t n, int64_t r0, const float *__restrict__ y,
                                                                   const int64_t *__restrict__ row_off,
                                                                   int32_t *__restrict__ out_col,
                                                                   float *__restrict__ out_val) {
     __shared__ int wave_tot[kSlotWaves];
-    const int64_t r = blockIdx.x;
+    const int64_t r = r0 + blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *row = y + r * n;
     const int64_t ob = row_off[r];
@@ -1219,12 +1219,12 @@ __global__ __launch_bounds__(kSlotThreads) void dense_to_rows_kernel(int64_t n, 
 // The same with four consecutive columns per thread (one 16-byte load; rows 16-byte aligned, n % 4 == 0): a
 // lane's survivor count (0-4) is scanned across the wave by three bit-sliced ballots, so an iteration covers
 // 4096 columns with the same two barriers.
-__global__ __launch_bounds__(kSlotThreads) void dense_to_rows4_kernel(int64_t n, const float *__restrict__ y,
+__global__ __launch_bounds__(kSlotThreads) void dense_to_rows4_kernel(int64_t n, int64_t r0, const float *__restrict__ y,
                                                                    const int64_t *__restrict__ row_off,
                                                                    int32_t *__restrict__ out_col,
                                                                    float *__restrict__ out_val) {
     __shared__ int wave_tot[kSlotWaves];
-    const int64_t r = blockIdx.x;
+    const int64_t r = r0 + blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float4 *row = reinterpret_cast<const float4 *>(y + r * n);
     const int64_t ob = row_off[r], n4 = n / 4;
@@ -1261,10 +1261,10 @@ __global__ __launch_bounds__(kSlotThreads) void dense_to_rows4_kernel(int64_t n,
 }
 
 // Nonzeros of each dense batch-major row, for packing the rows straight into CSR.
-__global__ __launch_bounds__(kSlotThreads) void dense_count_kernel(int64_t n, const float *__restrict__ y,
+__global__ __launch_bounds__(kSlotThreads) void dense_count_kernel(int64_t n, int64_t r0, const float *__restrict__ y,
                                                                 int32_t *__restrict__ cnt) {
     __shared__ int wave_tot[kSlotWaves];
-    const int64_t r = blockIdx.x;
+    const int64_t r = r0 + blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *row = y + r * n;
     int c = 0;
@@ -1434,16 +1434,23 @@ hipError_t launch_dense_to_csr(int64_t n, int64_t batch, const float *y, int32_t
                                int64_t *scan_tmp, const HostReport &report, int32_t *out_col, float *out_val,
                                hipStream_t s) {
     if (batch == 0) return hipErrorInvalidValue;
-    if (!counted) dense_count_kernel<<<(unsigned)batch, kSlotThreads, 0, s>>>(n, y, cnt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    constexpr int64_t kSeg = 1ll << 21;  // rows per launch: fewer than 2^32 work-items
+    hipError_t e = hipSuccess;
+    for (int64_t r0 = 0; r0 < batch && !counted; r0 += kSeg) {
+        dense_count_kernel<<<(unsigned)(batch - r0 < kSeg ? batch - r0 : kSeg), kSlotThreads, 0, s>>>(n, r0, y, cnt);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     e = launch_row_ptr(batch, cnt, row_ptr, scan_tmp, report, s);
-    if (e != hipSuccess) return e;
-    if (n % 4 == 0)
-        dense_to_rows4_kernel<<<(unsigned)batch, kSlotThreads, 0, s>>>(n, y, row_ptr, out_col, out_val);
-    else
-        dense_to_rows_kernel<<<(unsigned)batch, kSlotThreads, 0, s>>>(n, y, row_ptr, out_col, out_val);
-    return hipGetLastError();
+    for (int64_t r0 = 0; r0 < batch && e == hipSuccess; r0 += kSeg) {
+        const unsigned rows = (unsigned)(batch - r0 < kSeg ? batch - r0 : kSeg);
+        if (n % 4 == 0)
+            dense_to_rows4_kernel<<<rows, kSlotThreads, 0, s>>>(n, r0, y, row_ptr, out_col, out_val);
+        else
+            dense_to_rows_kernel<<<rows, kSlotThreads, 0, s>>>(n, r0, y, row_ptr, out_col, out_val);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace sdnn

@@ -44,3 +44,31 @@ def test_dense_batch_past_one_launch_of_the_resident_product():
         part = y[r:r + CHUNK]
         assert torch.equal(out[r:r + CHUNK], net.mxm(0, sd.SDNN_SEMIRING_MAX_PLUS, part, out=want[:part.shape[0]]))
     net.free()
+
+
+def test_csr_batch_past_one_launch_of_the_packing():
+    """4,194,304 rows of a 1024-thread workgroup each reach 2^32 work-items in the packing of a dense result."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    net = _net(sd)
+    batch = (1 << 22) + 1001
+    g = torch.Generator(device="cuda").manual_seed(2)
+    mask = torch.rand((batch, N), generator=g, device="cuda") < 1 / 16
+    rp = torch.zeros(batch + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(mask.sum(1), 0, out=rp[1:])
+    col = mask.nonzero()[:, 1].to(torch.int32)
+    val = torch.rand(col.numel(), generator=g, device="cuda") + 0.1
+    del mask
+    print("[case] large csr batch", batch, flush=True)
+    got_rp, got_col, got_val = (x.clone() for x in net.forward_csr(rp, col, val))
+    assert 0 < got_col.numel() == int(got_rp[-1])
+    for r in range(0, batch, CHUNK):
+        e = min(batch, r + CHUNK)
+        a, b = int(rp[r]), int(rp[e])
+        want = net.forward_csr(rp[r:e + 1] - a, col[a:b], val[a:b])
+        ga, gb = int(got_rp[r]), int(got_rp[e])
+        assert torch.equal(got_rp[r:e + 1] - ga, want[0])
+        assert torch.equal(got_col[ga:gb], want[1]) and torch.equal(got_val[ga:gb], want[2])
+    net.free()
