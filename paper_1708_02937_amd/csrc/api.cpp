@@ -70,6 +70,7 @@ struct Layer {
     int64_t pos_bias = 0;      // neurons with b_j > 0
     double zero_below = -INFINITY;  // every b_j <= 0: -max_j b_j (a sum at most this is zero after h), else -inf
     int32_t max_fanout = 0;    // longest fan-out row of W_k
+    int32_t max_fanin = 0;     // longest fan-in list
     Edge *w_pack = nullptr;    // fan-out entries packed as (column, weight)
     int64_t *fan_ptr = nullptr;  // fan-in CSR (W_k^T)
     Edge *fan = nullptr;
@@ -105,6 +106,8 @@ struct LayerPlan {
            resident = kAbsent, dense64 = kAbsent, dense32 = kAbsent;
     size_t bytes = 0;
 };
+
+constexpr int kSetupInts = 8;  // what a layer's set-up reports to the host (the first four also its validation's flags)
 
 struct NetPlan {
     size_t flags = 0, d_int = 0, stats = 0, counts = 0, tmp = 0, sort = 0;
@@ -149,7 +152,7 @@ NetPlan plan_net(int64_t n, int32_t L, const int64_t *caps, int32_t dense_flags)
     int64_t max_cap = 0;
     for (int32_t k = 0; k < L; ++k) max_cap = std::max(max_cap, caps[k]);
     np.flags = take(off, 4 * sizeof(uint32_t));
-    np.d_int = take(off, 4 * sizeof(int32_t));
+    np.d_int = take(off, kSetupInts * sizeof(int32_t));
     np.stats = take(off, (size_t)std::max<int32_t>(L, 1) * sdnn::kSpgemmStats * sizeof(unsigned long long));
     np.counts = take(off, (size_t)n * sizeof(int32_t));
     np.tmp = take(off, (size_t)sdnn::scan_tmp_elems(n) * sizeof(int64_t));
@@ -268,7 +271,7 @@ struct sdnn_net_s {
     int32_t *d_int = nullptr;
     unsigned long long *d_stats = nullptr;  // kSpgemmStats counters per layer of a forward call
     int num_cu = 256;
-    // pinned host memory: what the kernels of a CSR call report, and four words the set-up copies back
+    // pinned host memory: what the kernels of a CSR call report, and the words the set-up copies back
     sdnn::HostSlot *host = nullptr;
     uint32_t *host_words = nullptr;
     char *arena = nullptr;  // caller-owned device memory holding everything above and every layer's copies
@@ -358,6 +361,20 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
         }
     }
     return best <= gather;
+}
+
+// Samples a layer's neuron-major product computes (at least the batch, at most the pitch).
+int64_t layer_batch(const sdnn_net_s *net, const Layer &l, int64_t batch, int64_t ld) {
+    return sdnn::spmm_batch(net->n, l.nnz, l.max_fanin, l.tile_mask != nullptr, batch, ld, net->num_cu);
+}
+
+// Row pitch of the neuron-major buffers for layers [k0, k1).
+int64_t range_ld(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch) {
+    for (int32_t k = k0; k < k1; ++k) {
+        const Layer &l = net->layers[(size_t)k];
+        if (l.tile_mask || !sdnn::spmm_long_list(net->n, l.nnz, l.max_fanin, batch)) return sdnn::act_ld(net->n, batch);
+    }
+    return sdnn::act_ld_tight(net->n, batch);
 }
 
 bool overlap(const float *a, const float *b, size_t count) {
@@ -472,7 +489,7 @@ sdnn_status sdnn_net_create(sdnn_net *out, int64_t n, int32_t L, float ymax, con
         return fail(SDNN_ERR_UNSUPPORTED, std::string("built for gfx950, device is ") + prop.gcnArchName);
     sdnn_net net = new (std::nothrow) sdnn_net_s();
     if (!net) return fail(SDNN_ERR_OUT_OF_MEMORY, "host allocation failed");
-    if (const hipError_t e = hipHostMalloc((void **)&net->host, sizeof(sdnn::HostSlot) + 4 * sizeof(uint32_t), hipHostMallocDefault);
+    if (const hipError_t e = hipHostMalloc((void **)&net->host, sizeof(sdnn::HostSlot) + kSetupInts * sizeof(uint32_t), hipHostMallocDefault);
         e != hipSuccess) {
         delete net;
         (void)hipGetLastError();
@@ -531,7 +548,7 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
 
     // 1. validate on the device
     // (the flags and the set-up's integers are cleared together: d_int follows the flags in the arena)
-    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, (size_t)((char *)(net->d_int + 4) - (char *)net->d_flags), s));
+    SDNN_HIP(hipMemsetAsync(net->d_flags, 0, (size_t)((char *)(net->d_int + kSetupInts) - (char *)net->d_flags), s));
     SDNN_HIP(sdnn::launch_validate_layer(n, nnz, row_ptr, col_idx, val, bias, net->d_flags, s));
     const uint32_t *fl = net->host_words;
     SDNN_HIP(hipMemcpyAsync(net->host_words, net->d_flags, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -598,6 +615,7 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     SETUP_HIP(sdnn::launch_fanin_lists(n, nnz, row_ptr, col_idx, val, nl.fan, sort_scratch, s));
     SETUP_HIP(hipMemsetAsync(nl.fan + nnz, 0, sizeof(Edge), s));
     SETUP_HIP(sdnn::launch_max_segment(n, row_ptr, net->d_int, s));
+    SETUP_HIP(sdnn::launch_max_segment(n, nl.fan_ptr, net->d_int + 3, s));
     if (nl.w_seg) SETUP_HIP(sdnn::launch_window_seg(n, row_ptr, col_idx, nl.w_seg, s));
     if (nl.sched) {
         SETUP_HIP(sdnn::launch_blocked_order(n, nl.fan_ptr, nl.sched, s));
@@ -607,11 +625,12 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     if (nl.tile_mask) SETUP_HIP(sdnn::launch_spmm_tile_mask(n, nl.fan_ptr, nl.fan, nl.tile_mask, s));
     if (nl.slots) SETUP_HIP(sdnn::launch_spmm_slots(n, nl.fan_ptr, nl.fan, nl.slots, s));
     if (nl.resident) SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 2, s));
-    SETUP_HIP(hipMemcpyAsync(net->host_words, net->d_int, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    SETUP_HIP(hipMemcpyAsync(net->host_words, net->d_int, kSetupInts * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     SETUP_HIP(hipStreamSynchronize(s));
     nl.max_fanout = (int32_t)net->host_words[0];
     const int32_t region_max = (int32_t)net->host_words[1];
     nl.resident_blocks = (int32_t)net->host_words[2];
+    nl.max_fanin = (int32_t)net->host_words[3];
 #undef SETUP_HIP
     // the product stages each workgroup's lists in LDS when the longest region fits; otherwise it reads the
     // same staged copy entry by entry
@@ -755,7 +774,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             SDNN_HIP(hipMemcpyAsync(Y_out, Y_in, (size_t)batch * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
         return SDNN_OK;
     }
-    int64_t ld = sdnn::act_ld(n, batch);
+    int64_t ld = range_ld(net, k0, k1, batch);
     if (static_ws) {
         // the library's fixed scratch array of this device replaces the caller's workspace
         const ScratchSlot *slot = net->device < kMaxDevices ? &g_scratch[net->device] : nullptr;
@@ -829,8 +848,8 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
         const Layer &l = net->layers[(size_t)k];
         int kind = sdnn::kKernGather;
         SDNN_HIP(prof_begin(net, k, kind, &pr));
-        SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask, l.slots, l.bias,
-                                         net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
+        SDNN_HIP(sdnn::launch_spmm_fanin(n, layer_batch(net, l, batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask, l.slots,
+                                         l.bias, net->ymax, net->bias_pattern, buf[cur], buf[cur ^ 1], s, &kind));
         SDNN_HIP(prof_end(net, pr, kind));
         cur ^= 1;
     }
@@ -1014,7 +1033,7 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
         const int db = from_user ? 0 : cur;  // the input rows (if any) sit in buffer cur ^ 1
         // two buffers of n x batch floats at row pitch ld
         float *dense[2] = {reinterpret_cast<float *>(w.col[db]), w.val[db]};
-        const int64_t ld = sdnn::act_ld(n, batch);
+        const int64_t ld = range_ld(net, kd, k1, batch);
         ResidentPlan plan;
         int pr = -1;
         int dc = 0;
@@ -1048,7 +1067,7 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
                 const Layer &l = net->layers[(size_t)k];
                 int kind = sdnn::kKernGather;
                 SDNN_HIP(prof_begin(net, k, kind, &pr));
-                SDNN_HIP(sdnn::launch_spmm_fanin(n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask,
+                SDNN_HIP(sdnn::launch_spmm_fanin(n, layer_batch(net, l, batch, ld), ld, l.fan_ptr, l.fan, l.tile_mask,
                                                  l.slots, l.bias, net->ymax, net->bias_pattern, dense[dc],
                                                  dense[dc ^ 1], s, &kind));
                 SDNN_HIP(prof_end(net, pr, kind));
@@ -1118,7 +1137,9 @@ sdnn_status sdnn_mxm_dense(sdnn_net net, int32_t k, int32_t semiring, int64_t ba
     float *yt = (float *)ws;
     float *zt = (float *)((char *)ws + sdnn::act_bytes(n, ld));
     SDNN_HIP(sdnn::launch_transpose(Y, n, yt, ld, batch, n, s));  // batch x n -> n x batch
-    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, sdnn::act_batch(batch, ld), ld, l.fan_ptr, l.fan, yt, zt, s));
+    // rounded up to a multiple of four where that gives the gather two or four columns per lane
+    const int64_t up = (batch + 3) / 4 * 4;
+    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, up >= 128 && up <= ld ? up : batch, ld, l.fan_ptr, l.fan, yt, zt, s));
     SDNN_HIP(sdnn::launch_transpose(zt, ld, Z, n, n, batch, s));  // n x batch -> batch x n
     return SDNN_OK;
 }

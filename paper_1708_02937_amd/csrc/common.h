@@ -95,15 +95,6 @@ hipError_t launch_fanin_lists(int64_t n, int64_t nnz, const int64_t *row_ptr, co
 hipError_t launch_max_segment(int64_t n, const int64_t *ptr, int32_t *out, hipStream_t s);
 hipError_t launch_pack_edges(int64_t nnz, const int32_t *col, const float *val, Edge *out, hipStream_t s);
 
-// Samples the neuron-major products compute: the batch rounded up to a multiple of four when the pitch has room.
-// The samples past the batch hold whatever the buffer held and are not copied out; a sample depends on no other.
-// (An odd batch otherwise gathers one column per lane: n 9001, 60 entries per neuron, batch 333, four layers took 318 us
-// that way, 198 this.)
-inline int64_t act_batch(int64_t batch, int64_t ld) {
-    const int64_t b = (batch + 3) / 4 * 4;
-    return b <= ld ? b : batch;
-}
-
 // spmm.hip
 // rows x cols (row pitch in_ld >= cols) -> cols x rows (row pitch out_ld >= rows)
 hipError_t launch_transpose(const float *in, int64_t in_ld, float *out, int64_t out_ld, int64_t rows, int64_t cols,
@@ -121,6 +112,11 @@ hipError_t launch_spmm_slots(int64_t n, const int64_t *fan_ptr, const Edge *fan,
 // tile_mask / slots: the high fan-in structures when the layer has them (else null).
 // yt, zt: n x batch at row pitch ld (act_ld(n, batch)).
 // kind (may be null) receives which product kernel ran (a KernelKind).
+// Samples the layer's product computes: the batch, or the batch rounded up to a multiple of four where the pitch has
+// room and the product it then takes is the cheaper one (tiles: the layer has tile masks; longest: its longest list).
+// The samples past the batch hold whatever the buffer held and are not copied out; a sample depends on no other.
+bool spmm_long_list(int64_t n, int64_t nnz, int64_t longest, int64_t batch);  // one long list sets the gather's time
+int64_t spmm_batch(int64_t n, int64_t nnz, int64_t longest, bool tiles, int64_t batch, int64_t ld, int num_cu);
 hipError_t launch_spmm_fanin(int64_t n, int64_t batch, int64_t ld, const int64_t *fan_ptr, const Edge *fan,
                              const uint16_t *tile_mask, const double *slots, const float *bias, double ymax, int pattern,
                              const float *yt, float *zt, hipStream_t s, int *kind = nullptr);

@@ -281,7 +281,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int64_t nnz,
 
 __global__ void max_segment_kernel(int64_t n, const int64_t *__restrict__ ptr, int32_t *out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicMax(out, (int32_t)(ptr[i + 1] - ptr[i]));
+    int32_t len = i < n ? (int32_t)(ptr[i + 1] - ptr[i]) : 0;
+    for (int d = 32; d > 0; d >>= 1) len = max(len, __shfl_xor(len, d));
+    if (threadIdx.x % 64 == 0) atomicMax(out, len);
 }
 
 __global__ void pack_edges_kernel(int64_t nnz, const int32_t *__restrict__ col, const float *__restrict__ val,

@@ -11,6 +11,8 @@
 // XCD-aware launch: workgroups are dealt round-robin to the 8 XCDs, so the batch chunk follows from
 // blockIdx % 8.  Each XCD owns every eighth chunk and works through its chunks one at a time, so the
 // rows of Y^T that its current output neurons gather stay in that XCD's L2.
+#include <algorithm>
+
 #include "common.h"
 
 namespace sdnn {
@@ -762,6 +764,49 @@ hipError_t launch_spmm_tile_mask(int64_t n, const int64_t *fan_ptr, const Edge *
     if (e != hipSuccess) return e;
     tile_mask_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, fan_ptr, fan, tile_mask);
     return hipGetLastError();
+}
+
+// Microseconds measured on MI355X.  A batch that is no multiple of four runs on the gather at one column per lane, 64
+// samples of 53,000 entries per us (n 5200 to 12000), 0.05 us per entry of the longest list at least.  Rounded up:
+//  - layers of density 2/9 and more take the LDS-tiled products from 125 samples on, whose cost hardly depends on the
+//    density and the batch's share of 256 samples: n 5200, density 0.25, batch 125 640 us against 292, density 0.5,
+//    batch 251 706 against 1008.  Rounds of workgroups (64 neurons x 256 samples, dealt to the XCDs in eights) times
+//    tiles of 16 inputs at 1.76 + 1.21 density us.
+//  - the others take the narrow-chunk gather, or more columns per lane, which walk a single long list at 0.1 (n >= 4096)
+//    or 0.07 us per entry: n 12363, 8 lists of about 6200 entries, batch 29, two layers 1063 us against 654 (734 at the
+//    true batch in rows of the rounded pitch, so a range whose layers all have such lists keeps the tight one).
+//  - on layers wider than 20480 (a 64-sample slice of Y^T exceeds an XCD's L2) that lost where the last chunk of 64
+//    samples was mostly empty: n 32768, 32 entries each, batch 77 / 101 / 119 83 / 110 / 118 us against 79 / 97 / 106, and
+//    from 65537 neurons on also at 33 to 43 samples (1-3%); lists under 16 entries gain everywhere (0.71 to 0.89).
+// Elsewhere it is faster: n 9001, 60 entries each, batch 333, four layers 198 us against 318; n 131072, 32 entries,
+// batch 1 112 against 210.
+static double gather_us(int64_t nnz, int64_t longest, int64_t batch) {
+    return std::max((double)nnz * (double)((batch + 63) / 64) / 53e3, 0.05 * (double)longest);
+}
+
+bool spmm_long_list(int64_t n, int64_t nnz, int64_t longest, int64_t batch) {
+    return (n >= 4096 ? 0.1 : 0.07) * (double)longest > gather_us(nnz, longest, batch) + 5.0;
+}
+
+int64_t spmm_batch(int64_t n, int64_t nnz, int64_t longest, bool tiles, int64_t batch, int64_t ld, int num_cu) {
+    const int64_t up = (batch + 3) / 4 * 4;
+    if (up == batch || up > ld) return batch;
+    const double gather = gather_us(nnz, longest, batch);
+    if (tiles && up >= 128) {
+        const int64_t groups = (mask_pitch(n) / 64 + 7) / 8 * 8 * ((up + kTiledCB - 1) / kTiledCB);
+        const double tiled = (double)((groups + num_cu - 1) / num_cu) * (double)spmm_tile_count(n) *
+                             (1.76 + 1.21 * (double)nnz / ((double)n * (double)n));
+        return 1.1 * tiled <= gather ? up : batch;
+    }
+    if (spmm_long_list(n, nnz, longest, batch)) return batch;
+    if (n > 20480 && nnz >= 16 * n) {
+        const int64_t last = up % 64;  // samples in the last chunk
+        const bool sparse_chunk = last > 0 && last < (n > 65536 ? 44 : batch < 128 ? 60 : 56);
+        const int64_t from = n > 65536 ? 32 : n > 40960 ? 64 : n > 28672 ? 72 : 82;
+        if (sparse_chunk && batch > from && !(n <= 40960 && batch > 128 && batch <= 192))
+            return batch;
+    }
+    return up;
 }
 
 hipError_t launch_spmm_fanin(int64_t n, int64_t batch, int64_t ld, const int64_t *fan_ptr, const Edge *fan,

@@ -205,3 +205,35 @@ def test_scratch_array_without_room_for_rounding():
     sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, y, out, sd.SDNN_ARM_SPARSE)
     assert torch.equal(out, net.forward_dense(y))
     net.free()
+
+
+@pytest.mark.parametrize("n,batch,lists,want", [
+    (5200, 125, 0.25, "spmm_fanin_kernel"), (5200, 391, 0.25, "spmm_slots_kernel"), (5200, 251, 0.5, "spmm_slots_kernel"),
+    (6000, 7, [20], "spmm_narrow_kernel"), (6000, 7, [20] * 5999 + [3000], "spmm_fanin_kernel"),
+    (9000, 131, [10] * 4499 + [4000], "spmm_fanin_kernel"), (24000, 97, [32], "spmm_fanin_kernel"),
+    (24000, 61, [32], "spmm_narrow_kernel")])
+def test_ragged_batches_rounded_where_it_is_cheaper(n, batch, lists, want):
+    """A batch that is no multiple of four is rounded up for the LDS-tiled product or the narrow-chunk gather only where
+    they are the cheaper ones, and stays as it is on the plain gather otherwise: few samples at densities of a quarter, one
+    list of thousands of entries, a mostly empty last chunk of 64 samples on wide layers."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+    from workloads import tiny_random
+
+    if isinstance(lists, float):
+        p = tiny_random(n, n, 1, batch, w_density=lists, y_density=0.7, dense_input=True)
+    else:
+        p = _problem(n, batch, 1, lists, n)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    print("[case] ragged route", n, batch, want, flush=True)
+    net.set_profiling(True)
+    got = net.forward_dense(y).cpu().numpy()
+    assert [name for _, name, _ in net.read_profile()][1:-1] == [want]
+    out = torch.empty_like(y)
+    sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, y, out, sd.SDNN_ARM_SPARSE)
+    assert out.cpu().numpy().tobytes() == got.tobytes()
+    net.free()
+    rows = np.arange(0, batch, 1 + batch // 16)
+    parity.compare(p, dense_to_csr(got[rows]), rows=rows)
