@@ -82,6 +82,7 @@ struct Layer {
     sdnn::BlockedRegion *regions = nullptr;  // the regions (null when one exceeds the product's LDS capacity)
     void *resident = nullptr;    // lists interleaved for the LDS-resident product (n <= kResidentMaxN)
     int32_t resident_blocks = 0; // its blocks of four entries per lane
+    int32_t resident_wave = 0;   // blocks of a workgroup's busiest wave
     double *dense_wt = nullptr;  // n x n, W_k k-major in fp64 (zeros explicit), for the fp64 dense arm
     float *dense_wt32 = nullptr; // the same in fp32, for the fp32 dense arm
     bool dense_ready = false, dense32_ready = false;  // the dense copies hold the current W_k
@@ -301,6 +302,11 @@ bool use_blocked(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch) {
     return true;
 }
 
+// Samples a layer's neuron-major product computes (at least the batch, at most the pitch).
+int64_t layer_batch(const sdnn_net_s *net, const Layer &l, int64_t batch, int64_t ld) {
+    return sdnn::spmm_batch(net->n, l.nnz, l.max_fanin, l.tile_mask != nullptr, batch, ld, net->num_cu);
+}
+
 // How a dense-Y range runs on the LDS-resident product: samples per workgroup, workgroups per sample group (the
 // neurons split over them), and whether the whole range is one launch.
 struct ResidentPlan {
@@ -309,8 +315,10 @@ struct ResidentPlan {
 };
 
 // The rule, in microseconds measured on MI355X (n 300 to 5000, 16 to 819 entries per neuron, batch 33 to 2048).
-// A workgroup takes 0.0146, 0.0173 or 0.026 us per block of 4 x 64 entries at 1, 2 or 4 samples, a CU runs one
-// workgroup at a time, a fused range costs about 3 us and 1 us per layer beyond that, and a launch per layer 4.5.
+// A workgroup takes 0.015, 0.0163 or 0.0238 us per block of 4 x 64 entries at 1, 2 or 4 samples, a CU gets through
+// one workgroup's blocks at a time, a layer costs 0.85 us per run of 1024 neurons beyond that (n 4097, 12 entries,
+// batch 1, four layers: 33.8 us), a launch 2 to 3 us, and its rows in and out 0.12 per 1024 neurons and sample: once for
+// a fused range, in every round of workgroups where each layer is a launch.
 // So few samples per workgroup where that still fills the CUs once, four where the batch does so several times
 // over, and the neurons split over workgroups (then a launch per layer) where a small batch leaves CUs idle: one
 // layer of 4096 neurons and 64 entries each at batch 64 takes 23.7 us whole and 9.2 in four parts, four layers of
@@ -318,41 +326,73 @@ struct ResidentPlan {
 // per product from L2 (about 27 TB/s with four samples per lane, from batch 256 on, and 12 to 16 below) and cost 6 us
 // per layer and two transposes; they win only where the last round of workgroups is nearly empty.  The LDS-tiled
 // product of high fan-in layers takes 1.76 + 1.21 density us per tile of 16 inputs and round of workgroups (64 neurons
-// x 256 samples): 157 us per layer at n 1000, batch 129, where the resident product takes 40.  With profiling on every layer is a launch of its own, and ranges with a
+// x 256 samples): 157 us per layer at n 1000, batch 129, where the resident product takes 40.
+// A few long lists bound both: the wave that walks them in the resident product takes 0.095, 0.113 or 0.142 us per block
+// by itself (two workgroups share a CU at 1 and 2 samples where their LDS fits) and 0.6 of the even share beside it, and
+// the gather 0.055 to 0.11 us per entry beyond the mean, once per layer whatever the batch.  One list of 1459 entries in 2918 neurons,
+// batch 3045, four layers: 617 us at two samples per workgroup, 670 at four, 605 by the gather; one of 2048 in 4096,
+// batch 1024: 292, 308 and 603.
+// With profiling on every layer is a launch of its own, and ranges with a
 // layer of under 2^24 products stay on the neuron-major products: the one launch is what they gain from.
 bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, bool semiring,
                    ResidentPlan *plan) {
     const int64_t n = net->n;
     if (n > sdnn::kResidentMaxN) return false;
-    double blocks = 0.0, gather = 2.0 * (3.0 + 8.0 * (double)n * (double)batch / 4e6);
+    const double cus = (double)net->num_cu, size = (double)n, samples = (double)batch;
+    const int64_t ld = sdnn::act_ld(n, batch);
+    double gather = 6.0 + 4e-6 * size * samples;
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
-        const double products = (double)l.nnz * (double)batch;
+        const double nnz = (double)l.nnz;
         if (!l.resident) return false;
-        if (!semiring && net->profiling && products < (double)(1 << 24)) return false;  // (semirings are not logged)
-        blocks += (double)l.resident_blocks;
-        if (!semiring && l.slots && batch > 124) {
-            const double tiles = std::ceil((double)n / 16.0);
-            gather += 6.0 + std::ceil(std::ceil((double)n / 64.0) * std::ceil((double)batch / 256.0) / (double)net->num_cu) *
-                                tiles * (1.76 + 1.21 * (double)l.nnz / ((double)n * (double)n));
+        if (!semiring && net->profiling && nnz * samples < (double)(1 << 24)) return false;  // (semirings are not logged)
+        const int64_t lb = layer_batch(net, l, batch, ld);
+        if (!semiring && l.slots && lb % 4 == 0 && lb >= 128) {
+            gather += 6.0 + (double)(((n + 63) / 64 * ((batch + 255) / 256) + net->num_cu - 1) / net->num_cu) *
+                                (double)((n + 15) / 16) * (1.76 + 1.21 * nnz / (size * size));
+        } else if (lb % 4 != 0) {
+            gather += 6.0 + 1.5 * sdnn::spmm_gather_us(l.nnz, l.max_fanin, batch);
         } else {
-            gather += 6.0 + products / (batch > 252 ? 6.75e6 : n >= 4096 ? 4.1e6 : 3.0e6);
+            const double longest = (double)l.max_fanin;
+            const double entry = batch <= 252 ? (n >= 4096 ? 0.085 : 0.055)
+                                 : n > 4096   ? 0.11
+                                 : batch <= 1100 ? 0.068 : 0.1 - 0.045 * longest / size;
+            const int64_t chunks = (batch + 255) / 256;  // a power of two up to 8 keeps each on its own XCDs
+            const double rate = chunks <= 8 && 8 % chunks == 0 ? 6.75e6 : n > 1024 ? 4.5e6 : 6.75e6;
+            gather += 6.0 + nnz * (batch > 252 ? 256.0 * (double)chunks / rate : samples / (n >= 4096 ? 4.1e6 : 3.0e6)) +
+                      entry * std::max(0.0, longest - nnz / size);
         }
     }
     const int64_t runs = (n + 1023) / 1024;
-    const double layers = (double)(k1 - k0), cus = (double)net->num_cu;
-    const double per_block[] = {0.0146, 0.0173, 0.026};
+    const double layers = (double)(k1 - k0);
+    const double per_block[] = {0.015, 0.0163, 0.0238}, alone[] = {0.095, 0.113, 0.142};
+    auto up = [](double x) {  // the next whole number
+        const double whole = (double)(int64_t)x;
+        return whole < x ? whole + 1.0 : whole;
+    };
     double best = 0.0;
     for (int i = 0; i < 3; ++i) {
         const int v = 1 << i;
-        const double groups = (double)((batch + v - 1) / v);
-        for (int64_t parts = 1; parts <= (may_split ? runs : 1); ++parts) {
-            const double share = std::ceil((double)runs / (double)parts) / (double)runs;
-            const double rounds = std::ceil(groups * std::ceil((double)runs / std::ceil((double)runs / (double)parts)) / cus);
+        const int64_t groups = (batch + v - 1) >> i;
+        for (int32_t parts = 1; parts <= (may_split ? (int32_t)runs : 1); ++parts) {
+            const int32_t per = ((int32_t)runs + parts - 1) / parts;  // runs of a part
+            const double workgroups = (double)(groups * (((int32_t)runs + per - 1) / per));
+            const bool two = v < 4 && sdnn::resident_lds(n, v, parts == 1 ? n + 1 : per * 1024) <= sdnn::kResidentLds / 2;
+            const double load = std::max(1.0, workgroups / cus);
+            const double rounds = up(load), turns = two ? up(0.5 * load) : rounds;
+            const double block = per_block[i] * (double)per / (double)runs;
+            double t = 0.0;
+            for (int32_t k = k0; k < k1; ++k) {
+                const Layer &l = net->layers[(size_t)k];
+                const double blocks = (double)l.resident_blocks * block;
+                const double wave = (double)std::min(l.resident_wave, (l.max_fanin + 3) / 4 * per);
+                t += std::max(rounds * blocks + 0.5 * (rounds - 1.0),
+                              turns * alone[i] * wave + 0.6 * load * blocks + 0.5 * (turns - 1.0));
+            }
             const bool fused = parts == 1 && (semiring || !net->profiling);
-            const double t = rounds * blocks * share * per_block[i] + (fused ? 3.0 + layers : 4.5 * layers) +
-                             (rounds - 1.0) * layers * 0.5;
-            if (plan->v == 0 || t < best) {
+            const double rows = 0.12 * (double)(runs << i);
+            t += fused ? 2.0 + rows + 0.85 * (double)runs * layers : (3.0 + rounds * (rows + 0.85 * (double)per)) * layers;
+            if (plan->v == 0 || t < 0.98 * best) {  // near ties: fewer samples and parts
                 best = t;
                 plan->v = v;
                 plan->parts = (int)parts;
@@ -361,11 +401,6 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
         }
     }
     return best <= gather;
-}
-
-// Samples a layer's neuron-major product computes (at least the batch, at most the pitch).
-int64_t layer_batch(const sdnn_net_s *net, const Layer &l, int64_t batch, int64_t ld) {
-    return sdnn::spmm_batch(net->n, l.nnz, l.max_fanin, l.tile_mask != nullptr, batch, ld, net->num_cu);
 }
 
 // Row pitch of the neuron-major buffers for layers [k0, k1).
@@ -615,7 +650,7 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     SETUP_HIP(sdnn::launch_fanin_lists(n, nnz, row_ptr, col_idx, val, nl.fan, sort_scratch, s));
     SETUP_HIP(hipMemsetAsync(nl.fan + nnz, 0, sizeof(Edge), s));
     SETUP_HIP(sdnn::launch_max_segment(n, row_ptr, net->d_int, s));
-    SETUP_HIP(sdnn::launch_max_segment(n, nl.fan_ptr, net->d_int + 3, s));
+    SETUP_HIP(sdnn::launch_max_segment(n, nl.fan_ptr, net->d_int + 2, s));
     if (nl.w_seg) SETUP_HIP(sdnn::launch_window_seg(n, row_ptr, col_idx, nl.w_seg, s));
     if (nl.sched) {
         SETUP_HIP(sdnn::launch_blocked_order(n, nl.fan_ptr, nl.sched, s));
@@ -624,13 +659,14 @@ sdnn_status sdnn_net_set_layer(sdnn_net net, int32_t k, int64_t nnz, const int64
     }
     if (nl.tile_mask) SETUP_HIP(sdnn::launch_spmm_tile_mask(n, nl.fan_ptr, nl.fan, nl.tile_mask, s));
     if (nl.slots) SETUP_HIP(sdnn::launch_spmm_slots(n, nl.fan_ptr, nl.fan, nl.slots, s));
-    if (nl.resident) SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 2, s));
+    if (nl.resident) SETUP_HIP(sdnn::launch_resident_lists(n, nl.fan_ptr, nl.fan, nl.resident, net->d_int + 4, s));
     SETUP_HIP(hipMemcpyAsync(net->host_words, net->d_int, kSetupInts * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     SETUP_HIP(hipStreamSynchronize(s));
     nl.max_fanout = (int32_t)net->host_words[0];
     const int32_t region_max = (int32_t)net->host_words[1];
-    nl.resident_blocks = (int32_t)net->host_words[2];
-    nl.max_fanin = (int32_t)net->host_words[3];
+    nl.max_fanin = (int32_t)net->host_words[2];
+    nl.resident_blocks = (int32_t)net->host_words[4];
+    nl.resident_wave = (int32_t)net->host_words[5];
 #undef SETUP_HIP
     // the product stages each workgroup's lists in LDS when the longest region fits; otherwise it reads the
     // same staged copy entry by entry
@@ -774,7 +810,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             SDNN_HIP(hipMemcpyAsync(Y_out, Y_in, (size_t)batch * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
         return SDNN_OK;
     }
-    int64_t ld = range_ld(net, k0, k1, batch);
+    int64_t ld = sdnn::act_ld(n, batch);
     if (static_ws) {
         // the library's fixed scratch array of this device replaces the caller's workspace
         const ScratchSlot *slot = net->device < kMaxDevices ? &g_scratch[net->device] : nullptr;
@@ -840,6 +876,7 @@ static sdnn_status forward_dense_impl(sdnn_net net, int32_t k0, int32_t k1, int6
             return run_resident(net, k0, k1, batch, plan, io, buf);
         }
     }
+    ld = std::min(ld, range_ld(net, k0, k1, batch));
     SDNN_HIP(prof_begin(net, -1, sdnn::kKernTranspose, &pr));
     SDNN_HIP(sdnn::launch_transpose(Y_in, n, buf[0], ld, batch, n, s));  // batch x n -> n x batch
     SDNN_HIP(prof_end(net, pr));
@@ -1137,9 +1174,11 @@ sdnn_status sdnn_mxm_dense(sdnn_net net, int32_t k, int32_t semiring, int64_t ba
     float *yt = (float *)ws;
     float *zt = (float *)((char *)ws + sdnn::act_bytes(n, ld));
     SDNN_HIP(sdnn::launch_transpose(Y, n, yt, ld, batch, n, s));  // batch x n -> n x batch
-    // rounded up to a multiple of four where that gives the gather two or four columns per lane
+    // rounded up to a multiple of four where that gives the gather two or four columns per lane, unless one long list
+    // sets its time
     const int64_t up = (batch + 3) / 4 * 4;
-    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, up >= 128 && up <= ld ? up : batch, ld, l.fan_ptr, l.fan, yt, zt, s));
+    const bool round = up >= 128 && up <= ld && !sdnn::spmm_long_list(n, l.nnz, l.max_fanin, batch);
+    SDNN_HIP(sdnn::launch_semiring_mxm(semiring, n, round ? up : batch, ld, l.fan_ptr, l.fan, yt, zt, s));
     SDNN_HIP(sdnn::launch_transpose(zt, ld, Z, n, n, batch, s));  // n x batch -> batch x n
     return SDNN_OK;
 }

@@ -115,6 +115,7 @@ hipError_t launch_spmm_slots(int64_t n, const int64_t *fan_ptr, const Edge *fan,
 // Samples the layer's product computes: the batch, or the batch rounded up to a multiple of four where the pitch has
 // room and the product it then takes is the cheaper one (tiles: the layer has tile masks; longest: its longest list).
 // The samples past the batch hold whatever the buffer held and are not copied out; a sample depends on no other.
+double spmm_gather_us(int64_t nnz, int64_t longest, int64_t batch);  // estimate of the gather at one column per lane
 bool spmm_long_list(int64_t n, int64_t nnz, int64_t longest, int64_t batch);  // one long list sets the gather's time
 int64_t spmm_batch(int64_t n, int64_t nnz, int64_t longest, bool tiles, int64_t batch, int64_t ld, int num_cu);
 hipError_t launch_spmm_fanin(int64_t n, int64_t batch, int64_t ld, const int64_t *fan_ptr, const Edge *fan,
@@ -125,6 +126,9 @@ hipError_t launch_spmm_fanin(int64_t n, int64_t batch, int64_t ld, const int64_t
 // out, a range of layers per launch), for layers of at most kResidentMaxN neurons.
 constexpr int kResidentMaxN = 5119;   // two LDS buffers of n + 1 rows of four samples
 constexpr int kResidentLayers = 32;   // layers per launch
+constexpr size_t kResidentLds = 160 * 1024;
+// LDS of a workgroup: v samples of the inputs and the zero row, and out_rows rows of outputs
+inline size_t resident_lds(int64_t n, int v, int64_t out_rows) { return (size_t)(n + 1 + out_rows) * (size_t)v * 4; }
 struct ResidentLayer {
     const char *blocks;     // interleaved lists, blocks of four entries per lane
     const uint2 *slices;    // first block and block count of every 64-neuron slice
@@ -134,8 +138,8 @@ struct ResidentLayer {
 bool resident_planned(int64_t n);     // set-up builds a layer's interleaved lists
 size_t resident_bytes(int64_t n, int64_t nnz);
 ResidentLayer resident_layer(void *mem, int64_t n, const float *bias);
-// total (device) receives the number of blocks
-hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *total,
+// report (device) receives the number of blocks and those of the busiest wave of a workgroup
+hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *report,
                                  hipStream_t s);
 // Input: y_in (batch x n), or sparse rows (caller CSR, extents and columns checked into err; or slot rows with
 // counts: row r at r * n).  Output: y_out, and per sample its nonzeros when cnt_out is not null (one part only).

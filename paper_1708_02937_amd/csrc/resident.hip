@@ -36,7 +36,11 @@ constexpr int kRunLen = 1024;             // neurons sorted together: one slice 
 constexpr int kRunSlices = kRunLen / 64;
 static_assert(kRunSlices == kRWaves, "a run is one slice per wave");
 constexpr int kBlockBytes = 64 * 4 * (2 + 4);
-constexpr int kMaxLds = 160 * 1024;
+
+// Slices of a run are ordered by length: a wave alternates between their ends.
+__device__ __forceinline__ int slice_of(int run, int wave) {
+    return run * kRunSlices + ((run & 1) ? kRunSlices - 1 - wave : wave);
+}
 
 // ------------------------------------------------------------------------------------------ set-up
 
@@ -73,11 +77,11 @@ __global__ __launch_bounds__(kRunLen) void resident_order_kernel(int64_t n, cons
 
 // Blocks of every slice: a wave takes blocks blockIdx.y, + gridDim.y, ... of its slice.  The slice's first block is
 // the sum of the counts before it, which every wave adds up for itself (at most 80 slices); the first wave of a slice
-// writes it down, the last slice's the total.
+// writes it down, the last slice's the total, and the first slice's the blocks of the product's busiest wave.
 __global__ __launch_bounds__(64) void resident_fill_kernel(int64_t n, const int64_t *__restrict__ fan_ptr,
                                                            const Edge *__restrict__ fan,
                                                            const uint16_t *__restrict__ order, uint2 *slices,
-                                                           char *__restrict__ blocks, int32_t *__restrict__ total) {
+                                                           char *__restrict__ blocks, int32_t *__restrict__ report) {
     const int lane = threadIdx.x;
     uint32_t before = 0;
     for (uint32_t q = lane; q < blockIdx.x; q += 64) before += slices[q].y & 0xffffu;
@@ -85,7 +89,14 @@ __global__ __launch_bounds__(64) void resident_fill_kernel(int64_t n, const int6
     const uint2 sl = make_uint2(before, slices[blockIdx.x].y);
     if (lane == 0 && blockIdx.y == 0) {
         slices[blockIdx.x].x = before;
-        if (blockIdx.x + 1 == gridDim.x) *total = (int32_t)(before + (sl.y & 0xffffu));
+        if (blockIdx.x + 1 == gridDim.x) report[0] = (int32_t)(before + (sl.y & 0xffffu));
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        uint32_t wave = 0;
+        for (int run = 0; lane < kRWaves && run * kRunSlices < (int)gridDim.x; ++run)
+            wave += slices[slice_of(run, lane)].y & 0xffffu;
+        for (int d = 32; d > 0; d >>= 1) wave = max(wave, (uint32_t)__shfl_xor(wave, d));
+        if (lane == 0) report[1] = (int32_t)wave;
     }
     const uint32_t j = order[(int64_t)blockIdx.x * 64 + lane];
     int64_t e0 = 0;
@@ -238,15 +249,13 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
     const int run1 = min(run0 + runs, (nslices + kRunSlices - 1) / kRunSlices);
     const int j0 = run0 * kRunLen;  // first neuron of the part: its outputs sit at dst[j - j0]
 
-    // slices of a run are ordered by length: a wave alternates between its ends
-    auto slice_of = [&](int run) { return run * kRunSlices + ((run & 1) ? kRunSlices - 1 - wave : wave); };
     auto load = [&](const char *blocks, uint32_t b, uint2 &i, float4 &w) {
         const char *p = blocks + (size_t)b * kBlockBytes;  // wave-uniform: a scalar base and 32-bit lane offsets
         i = *reinterpret_cast<const uint2 *>(p + (uint32_t)lane * 8u);
         w = *reinterpret_cast<const float4 *>(p + (512u + (uint32_t)lane * 16u));
     };
     auto fetch = [&](const ResidentLayer &l, int run, Slice &s) {
-        const int q = slice_of(run);
+        const int q = slice_of(run, wave);
         s.count = s.whole = 0;
         s.first = 0;
         s.j = 0xffffu;
@@ -425,8 +434,6 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
 
 int64_t resident_slices(int64_t n) { return (n + kRunLen - 1) / kRunLen * kRunSlices; }
 
-size_t lds_bytes(int64_t n, int v, int64_t out_rows) { return (size_t)(n + 1 + out_rows) * v * 4; }
-
 }  // namespace
 
 // Bytes of a layer's interleaved lists: the order and slice table, then the blocks.  Lists of a run are sorted by
@@ -452,7 +459,7 @@ ResidentLayer resident_layer(void *mem, int64_t n, const float *bias) {
     return l;
 }
 
-hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *total,
+hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *fan, void *mem, int32_t *report,
                                  hipStream_t s) {
     const ResidentLayer l = resident_layer(mem, n, nullptr);
     const int64_t slices = resident_slices(n);
@@ -461,7 +468,7 @@ hipError_t launch_resident_lists(int64_t n, const int64_t *fan_ptr, const Edge *
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     resident_fill_kernel<<<dim3((unsigned)slices, 16), 64, 0, s>>>(
-        n, fan_ptr, fan, l.order, const_cast<uint2 *>(l.slices), const_cast<char *>(l.blocks), total);
+        n, fan_ptr, fan, l.order, const_cast<uint2 *>(l.slices), const_cast<char *>(l.blocks), report);
     return hipGetLastError();
 }
 
@@ -473,10 +480,10 @@ hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t bat
     const int64_t runs = (n + kRunLen - 1) / kRunLen;
     const int per = (int)((runs + parts - 1) / parts);
     parts = (int)((runs + per - 1) / per);
-    const size_t lds = lds_bytes(n, V, parts > 1 ? (int64_t)per * kRunLen : n + 1);
-    if (lds > (size_t)kMaxLds) return hipErrorInvalidValue;
+    const size_t lds = resident_lds(n, V, parts > 1 ? (int64_t)per * kRunLen : n + 1);
+    if (lds > kResidentLds) return hipErrorInvalidValue;
     static std::atomic<unsigned long long> attr_devices{0};
-    const hipError_t e = raise_lds_limit((const void *)spmm_resident_kernel<V, Op>, kMaxLds, attr_devices);
+    const hipError_t e = raise_lds_limit((const void *)spmm_resident_kernel<V, Op>, kResidentLds, attr_devices);
     if (e != hipSuccess) return e;
     const int64_t groups = (batch + V - 1) / V;
     const int64_t seg = (int64_t(1) << 21) / parts;  // groups per launch: fewer than 2^32 work-items

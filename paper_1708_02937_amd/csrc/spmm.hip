@@ -772,26 +772,27 @@ hipError_t launch_spmm_tile_mask(int64_t n, const int64_t *fan_ptr, const Edge *
 //    density and the batch's share of 256 samples: n 5200, density 0.25, batch 125 640 us against 292, density 0.5,
 //    batch 251 706 against 1008.  Rounds of workgroups (64 neurons x 256 samples, dealt to the XCDs in eights) times
 //    tiles of 16 inputs at 1.76 + 1.21 density us.
-//  - the others take the narrow-chunk gather, or more columns per lane, which walk a single long list at 0.1 (n >= 4096)
-//    or 0.07 us per entry: n 12363, 8 lists of about 6200 entries, batch 29, two layers 1063 us against 654 (734 at the
+//  - the others take the narrow-chunk gather or more columns per lane, which walk a single long list at 0.1 or 0.07 us
+//    per entry: n 12363, 8 lists of about 6200 entries, batch 29, two layers 1063 us against 654 (734 at the
 //    true batch in rows of the rounded pitch, so a range whose layers all have such lists keeps the tight one).
 //  - on layers wider than 20480 (a 64-sample slice of Y^T exceeds an XCD's L2) that lost where the last chunk of 64
 //    samples was mostly empty: n 32768, 32 entries each, batch 77 / 101 / 119 83 / 110 / 118 us against 79 / 97 / 106, and
 //    from 65537 neurons on also at 33 to 43 samples (1-3%); lists under 16 entries gain everywhere (0.71 to 0.89).
 // Elsewhere it is faster: n 9001, 60 entries each, batch 333, four layers 198 us against 318; n 131072, 32 entries,
 // batch 1 112 against 210.
-static double gather_us(int64_t nnz, int64_t longest, int64_t batch) {
+double spmm_gather_us(int64_t nnz, int64_t longest, int64_t batch) {
     return std::max((double)nnz * (double)((batch + 63) / 64) / 53e3, 0.05 * (double)longest);
 }
 
 bool spmm_long_list(int64_t n, int64_t nnz, int64_t longest, int64_t batch) {
-    return (n >= 4096 ? 0.1 : 0.07) * (double)longest > gather_us(nnz, longest, batch) + 5.0;
+    const double entry = n > 4096 || (n == 4096 && batch < 253) ? 0.1 : 0.07;
+    return entry * (double)longest > 1.2 * spmm_gather_us(nnz, longest, batch) + 5.0;
 }
 
 int64_t spmm_batch(int64_t n, int64_t nnz, int64_t longest, bool tiles, int64_t batch, int64_t ld, int num_cu) {
     const int64_t up = (batch + 3) / 4 * 4;
     if (up == batch || up > ld) return batch;
-    const double gather = gather_us(nnz, longest, batch);
+    const double gather = spmm_gather_us(nnz, longest, batch);
     if (tiles && up >= 128) {
         const int64_t groups = (mask_pitch(n) / 64 + 7) / 8 * 8 * ((up + kTiledCB - 1) / kTiledCB);
         const double tiled = (double)((groups + num_cu - 1) / num_cu) * (double)spmm_tile_count(n) *

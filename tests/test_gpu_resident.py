@@ -237,3 +237,54 @@ def test_ragged_batches_rounded_where_it_is_cheaper(n, batch, lists, want):
     net.free()
     rows = np.arange(0, batch, 1 + batch // 16)
     parity.compare(p, dense_to_csr(got[rows]), rows=rows)
+
+
+@pytest.mark.parametrize("lists,want", [([10] * 699 + [700], "spmm_fanin_kernel"), ([20], "spmm_resident_kernel")])
+def test_one_long_list_is_priced(lists, want):
+    """One list of all 700 inputs among lists of 10: the wave that walks it sets the resident product's time in every
+    round of workgroups, and the gather's once; without it the resident product is the cheaper one."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    batch = 3000
+    p = _problem(700, batch, 1, lists, 1)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    print("[case] one long list", want, flush=True)
+    got = net.forward_dense(y).cpu().numpy()
+    net.set_profiling(True)
+    logged = net.forward_dense(y).cpu().numpy()
+    assert want in [name for _, name, _ in net.read_profile()]
+    net.free()
+    assert got.tobytes() == logged.tobytes()
+    rows = np.arange(0, batch, 37)
+    parity.compare(p, dense_to_csr(got[rows]), rows=rows)
+
+
+@pytest.mark.parametrize("n,batch,L,lengths", [(157, 3667, 5, [1] * 156 + [78]), (2918, 301, 2, [10] * 700 + [1459]),
+                                               (5000, 13, 2, [10] * 249 + [1000]), (4339, 85, 2, [10] * 130 + [2170])])
+def test_few_long_lists(n, batch, L, lengths):
+    """A few lists far longer than the rest, on whichever products they are priced into: dense and CSR input against the
+    oracle, max.+ against numpy."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+    from workloads import csr_rows
+
+    p = _problem(n, batch, L, lengths, n)
+    net = sd.net_from_problem(p)
+    y = torch.from_numpy(p.y0_dense).cuda()
+    print("[case] few long lists", n, batch, L, flush=True)
+    rows = np.arange(0, batch, 1 + batch // 64)
+    parity.compare(p, dense_to_csr(net.forward_dense(y).cpu().numpy()[rows]), rows=rows)
+    csr = tuple(x.cpu().numpy() for x in net.forward_csr(*p.y0_as_csr()))
+    parity.compare(p, csr_rows(csr, rows), rows=rows)
+    z = net.mxm(0, sd.SDNN_SEMIRING_MAX_PLUS, y).cpu().numpy()
+    net.free()
+    l = p.layers[0]
+    i = np.repeat(np.arange(n), np.diff(l.row_ptr))
+    for r in (0, batch // 2, batch - 1):
+        want = np.full(n, -np.inf, dtype=np.float32)
+        np.maximum.at(want, l.col, p.y0_dense[r, i] + l.val)
+        assert np.array_equal(z[r], want)
