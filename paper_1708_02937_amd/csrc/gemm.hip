@@ -62,7 +62,9 @@ __host__ __device__ __forceinline__ int quad_neuron<double>(int q, int v) {
 // ------------------------------------------------------------------------------------------ layout changes
 
 // batch-major <-> [k block][q][sample][4], R samples x R neurons per workgroup through LDS (padded pitch): R = 64 moves
-// whole 256-byte segments, 32 gives small batches enough workgroups (4096 neurons, 64 samples: 7.2 us at 64, 4.8 at 32).
+// whole 256-byte segments, 32 gives small batches enough workgroups (4096 neurons, 64 samples: 7.2 us at 64, 4.8 at 32)
+// and more loads in flight on the way in (2048 neurons, 1024 samples: 8.5 us at 64, 5.6 at 32; the way out 5.5 at
+// either).
 template <typename T, int R>
 __global__ __launch_bounds__(256) void to_quads_kernel(int64_t n, int64_t batch, const float *__restrict__ y,
                                                        float4 *__restrict__ yq) {
@@ -170,19 +172,6 @@ struct Arm<double> {
         return activate(z + (double)bias, ymax);
     }
 };
-
-__device__ __forceinline__ void unit_values(const floatx4 (&u)[1], float (&a)[4]) {
-    a[0] = u[0].x;
-    a[1] = u[0].y;
-    a[2] = u[0].z;
-    a[3] = u[0].w;
-}
-__device__ __forceinline__ void unit_values(const doublex2 (&u)[2], double (&a)[4]) {
-    a[0] = u[0].x;
-    a[1] = u[0].y;
-    a[2] = u[1].x;
-    a[3] = u[1].y;
-}
 
 // kc: k blocks per split.  C in the activation layout (blocks = k blocks of the layer), or this split's sums in the same
 // order (fp64: two planes of two values) when partial is not null.
@@ -392,7 +381,7 @@ namespace {
 
 template <typename T>
 hipError_t launch_quads(int64_t n, int64_t batch, bool to, const float *in, float *out, hipStream_t s) {
-    const int64_t R = n * batch <= (int64_t(1) << 20) ? 32 : 64, cols = to ? gemm_k_blocks(n) * BK : n;
+    const int64_t R = n * batch <= (int64_t(1) << (to ? 24 : 20)) ? 32 : 64, cols = to ? gemm_k_blocks(n) * BK : n;
     const dim3 grid((unsigned)((batch + R - 1) / R), (unsigned)((cols + R - 1) / R));
     if ((cols + R - 1) / R > 65535) return hipErrorInvalidValue;
     if (to && R == 32)

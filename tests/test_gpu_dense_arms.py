@@ -81,3 +81,23 @@ def test_scratch_array_parts_keep_the_splits(arm, n, batch):
         sd.sdnn_forward_dense_noalloc(net.handle, 0, 1, batch, src, out, code)
         assert torch.equal(out, want)
     net.free()
+
+
+@pytest.mark.parametrize("arm", ["f64", "f32"])
+def test_layout_changes_of_large_batches(arm):
+    """Beyond 2^24 values the batch goes into the operand layout in 64 x 64 tiles, below in 32 x 32: the rows of a large
+    batch in two calls, bit for bit (no K splits at either size)."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    n, batch = 1001, 16799
+    p = tiny_random(4, n, 1, 4, w_density=0.02, dense_input=True)
+    code, flag = {"f64": (sd.SDNN_ARM_DENSE, 1), "f32": (sd.SDNN_ARM_DENSE_F32, 2)}[arm]
+    net = sd.net_from_problem(p, dense=flag)
+    y = torch.from_numpy(np.random.default_rng(5).random((batch, n), dtype=np.float32)).cuda()
+    print("[case] layout changes", arm, flush=True)
+    whole = net.forward_dense(y, arm=code)
+    assert torch.equal(whole[:8001], net.forward_dense(y[:8001], arm=code))
+    assert torch.equal(whole[8001:], net.forward_dense(y[8001:], arm=code))
+    net.free()
