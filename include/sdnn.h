@@ -29,7 +29,9 @@
  *     device current while it runs and restores the caller's device before it
  *     returns.  All device memory is the caller's (the net arena, workspaces,
  *     operands); the library allocates none, apart from the fixed scratch array
- *     behind sdnn_forward_dense_noalloc, and frees none.
+ *     behind sdnn_forward_dense_noalloc, and frees none.  A net holds 48 bytes of
+ *     pinned host memory from sdnn_net_create to sdnn_net_free, which its kernels
+ *     report counts and flags through.
  *   - CSR matrices use int64 row_ptr (rows + 1 entries, row_ptr[0] = 0),
  *     int32 column indices strictly increasing within a row, fp32 values.
  *   - Work is enqueued on the net's HIP stream and is asynchronous unless the
@@ -115,7 +117,8 @@ sdnn_status sdnn_net_arena_size(int64_t n, int32_t L, const int64_t *nnz_per_lay
  * memory for the net, now or later.  `stream` is a hipStream_t (NULL = the default stream).  *net receives
  * a host handle owned by the caller; release it with sdnn_net_free.  Checks the device is a gfx950 part.
  * Errors: NULL_POINTER, INVALID_VALUE (n < 1, n > 2^31-1, L < 0, ymax <= 0 or NaN, bad capacities or
- * flags, arena misaligned), WORKSPACE_TOO_SMALL (arena_bytes below sdnn_net_arena_size), UNSUPPORTED, DEVICE.
+ * flags, arena misaligned), WORKSPACE_TOO_SMALL (arena_bytes below sdnn_net_arena_size), OUT_OF_MEMORY (host or
+ * pinned host memory), UNSUPPORTED, DEVICE.
  */
 sdnn_status sdnn_net_create(sdnn_net *net, int64_t n, int32_t L, float ymax, const int64_t *nnz_per_layer,
                             int32_t dense_flags, void *arena, int64_t arena_bytes, void *stream);

@@ -48,6 +48,16 @@ struct DeviceScope {
     DeviceScope &operator=(const DeviceScope &) = delete;
 };
 
+// Allows the calling thread's allocation calls while another thread records a graph (a capture in global mode would
+// otherwise be broken by them).
+struct CaptureScope {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    CaptureScope() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~CaptureScope() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    CaptureScope(const CaptureScope &) = delete;
+    CaptureScope &operator=(const CaptureScope &) = delete;
+};
+
 #define SDNN_ON_DEVICE(net)                                                     \
     DeviceScope device_scope_((net)->device);                                   \
     if (device_scope_.err != hipSuccess) return fail_hip(device_scope_.err, "hipSetDevice")
@@ -524,6 +534,7 @@ sdnn_status sdnn_net_create(sdnn_net *out, int64_t n, int32_t L, float ymax, con
         return fail(SDNN_ERR_UNSUPPORTED, std::string("built for gfx950, device is ") + prop.gcnArchName);
     sdnn_net net = new (std::nothrow) sdnn_net_s();
     if (!net) return fail(SDNN_ERR_OUT_OF_MEMORY, "host allocation failed");
+    const CaptureScope capture_scope;
     if (const hipError_t e = hipHostMalloc((void **)&net->host, sizeof(sdnn::HostSlot) + kSetupInts * sizeof(uint32_t), hipHostMallocDefault);
         e != hipSuccess) {
         delete net;
