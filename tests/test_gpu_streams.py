@@ -1,7 +1,8 @@
-"""Nets beside a graph capture."""
+"""Nets beside a graph capture, and calls whose output overlaps their input."""
 
 import threading
 
+import numpy as np
 import pytest
 
 from workloads import tiny_random
@@ -51,4 +52,33 @@ def test_net_created_while_another_thread_captures():
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert torch.equal(net.forward_dense(y), want)
+    net.free()
+
+
+@pytest.mark.parametrize("n,batch,arm", [(300, 50, 0), (3000, 520, 0), (5200, 131, 0), (4500, 300, 0), (300, 50, 1), (300, 50, 2),
+                                         (700, 40, "mxm"), (6000, 40, "mxm")])
+def test_output_overlapping_the_input(n, batch, arm):
+    """Y_out a few rows or elements before or after Y_in, on every product: as with an output of its own."""
+    import torch
+
+    import paper_1708_02937_amd as sd
+
+    p = tiny_random(13, n, 2, 4, w_density=20 / n, dense_input=True, bias_lo=-0.1, bias_hi=0.1)
+    net = sd.net_from_problem(p, dense=arm if arm in (1, 2) else 0)
+    y = torch.from_numpy(np.random.default_rng(n).random((batch, n), dtype=np.float32)).cuda()
+
+    def call(src, dst):
+        if arm == "mxm":
+            return net.mxm(0, sd.SDNN_SEMIRING_MAX_PLUS, src, out=dst)
+        return net.forward_dense(src, arm=arm, out=dst)
+
+    want = call(y, torch.empty_like(y))
+    for shift in (3 * n, -3 * n, 7, -7):
+        print("[case] overlap", n, batch, arm, shift, flush=True)
+        room = torch.empty(batch * n + 3 * n, device="cuda")
+        lo = max(0, -shift)
+        src = room[lo:lo + batch * n].view(batch, n)
+        src.copy_(y)
+        dst = room[lo + shift:lo + shift + batch * n].view(batch, n)
+        assert torch.equal(call(src, dst), want)
     net.free()
