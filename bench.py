@@ -134,7 +134,7 @@ def kernel_sources(kernel):
     if kernel.startswith("spmm_resident"):
         return ["resident.hip", "common.h"]
     if kernel.startswith("gemm"):
-        return ["gemm.hip", "common.h"]
+        return ["gemm.hip", "common.h", "sizes.h"]
     if kernel.startswith("spgemm"):
         return ["spgemm.hip", "common.h"]
     return ["spmm.hip", "common.h"]
@@ -174,6 +174,23 @@ def kernel_roofline(name, rec, p, trace=None):
     roof["frac"] = round(roof["achieved"] / roof["peak"], 4)
     roof.update({"kernel": name, "launches": len(launches), "avg_launch_ms": round(rec["avg_ms"], 5),
                  "algorithmic_bytes_per_launch": int(byt), "algorithmic_flops_per_launch": flops})
+    return roof
+
+
+def forward_roofline(p, ms, steps):
+    """Roofline of a whole dense-batch forward: the batch read and written once and every layer's weights, list pointers
+    and bias read once (two operations per product), over the timed forward.  The profiling log cannot give it: while
+    it records, a range that otherwise runs as one launch runs layer by layer, small layers on other kernels."""
+    nnz = sum(l.nnz for l in p.layers)
+    byt = 8 * p.n * p.batch + 8 * nnz + (8 * (p.n + 1) + 4 * p.n) * len(p.layers)
+    flops = 2.0 * p.batch * nnz
+    roof = {"bound": "hbm", "achieved": round(byt / (ms / 1e3) / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s"}
+    if flops / byt > FP64_VECTOR_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9):
+        roof = {"bound": "alu", "achieved": round(flops / (ms / 1e3) / 1e12, 3), "peak": FP64_VECTOR_TFLOPS,
+                "unit": "TFLOP/s"}
+    roof["frac"] = round(roof["achieved"] / roof["peak"], 4)
+    roof.update({"kernel": "forward", "launches": steps, "avg_launch_ms": round(ms, 5),
+                 "algorithmic_bytes_per_launch": int(byt), "algorithmic_flops_per_launch": flops, "traffic": None})
     return roof
 
 
@@ -225,11 +242,14 @@ def run_sweep(args, torch, sd):
 
     for _ in range(args.warmup):
         step()
-    for net in nets:
-        net.set_profiling(True)
     t_wall = time.perf_counter()
     ms_step, ms_med, ms_min = time_steps(torch, step, args.steps)
     t_wall = time.perf_counter() - t_wall
+    # the log in a pass of its own: while it records, every layer is a launch
+    for net in nets:
+        net.set_profiling(True)
+    for _ in range(args.steps):
+        step()
     splits = []
     for net in nets:
         net.set_profiling(False)
@@ -238,13 +258,14 @@ def run_sweep(args, torch, sd):
     value = edges / (ms_step / 1e3)
     log(f"step {ms_step:.3f} ms (wall {1e3 * t_wall / args.steps:.3f} ms), {value:.4g} edges/s")
 
-    # per-density forward time, and the average launch time of the layer kernel over the timed steps
+    # per-density forward time and its share per layer, and the average time of one layer as a launch of its own
     sweep = {}
     reps = max(3, args.steps)
     for d, net, y, o, p, sp in zip(densities, nets, ys, outs, probs, splits):
         t_full = time_calls(torch, lambda: net.forward_dense(y, out=o), reps)
         kname = next(k for k in sp if k != "transpose_kernel")
         sweep[f"{d:g}"] = {"sparse_ms": round(t_full, 4), "sparse_edges_per_s": p.edges() / (t_full / 1e3),
+                           "layer_ms": round(t_full / p.L, 5),
                            "layer_kernel": kname, "layer_launch_ms": round(sp[kname]["avg_ms"], 5),
                            "nnz_per_layer": int(p.layers[0].nnz)}
 
@@ -512,8 +533,8 @@ PMC_TAGS = {1: "tiny-mlp", 3: "sparse-activation", 4: "deep-sparse", 5: "very-wi
 
 def run_csr_config(args, torch, sd):
     """Configs 3-5 (CSR input through sdnn_forward_csr) and config 1 (dense batch), one forward per step.
-    The library's profiling log is on during the timed steps (config 1: during an extra pass of the same
-    steps, so the event records do not weigh on a 30 us forward)."""
+    The library's profiling log is on during the timed steps (config 1: during an extra pass, layer by layer, which
+    is not the timed forward: its kernel times are recorded as such, and the roofline is the whole forward's)."""
     from workloads import make_config
 
     t0 = time.time()
@@ -539,7 +560,7 @@ def run_csr_config(args, torch, sd):
     ms, ms_med, ms_min = time_steps(torch, fn, args.steps)
     if not profiled_inline:
         net.set_profiling(True)
-        time_steps(torch, fn, args.steps)
+        layerwise_ms, _, _ = time_steps(torch, fn, args.steps)
     net.set_profiling(False)
     split = kernel_split(net.read_profile())
     log(f"step {ms:.3f} ms; " + ", ".join(f"{k} {v['launches']} x {v['avg_ms']:.4f} ms" for k, v in split.items()))
@@ -553,7 +574,8 @@ def run_csr_config(args, torch, sd):
         # the graph holds the net's buffers: release it, with its work finished, before the net is freed
         torch.cuda.synchronize()
         del g
-        extra = {"eager_ms_per_step": round(ms, 4), "graph_ms_per_step": round(timed[0], 4)}
+        extra = {"eager_ms_per_step": round(ms, 4), "graph_ms_per_step": round(timed[0], 4),
+                 "layerwise_ms_per_step": round(layerwise_ms, 4)}
         log(f"eager {ms:.4f} ms, graph replay {timed[0]:.4f} ms per forward")
         if timed[0] < ms:
             ms, ms_med, ms_min = timed
@@ -568,9 +590,14 @@ def run_csr_config(args, torch, sd):
     torch.cuda.synchronize()
     per_step = {k: round(v["total_ms"] / args.steps, 4) for k, v in split.items()}
     dom = max(split, key=lambda k: split[k]["total_ms"])
-    roof = kernel_roofline(dom, split[dom], p, trace)
-    hbm = None
-    if roof is not None:
+    if p.y0_csr is None:
+        extra["layerwise_kernel_ms_per_step"], per_step = per_step, None
+        roof = forward_roofline(p, ms, args.steps)
+        hbm = hbm_fields(roof, None)
+    else:
+        roof = kernel_roofline(dom, split[dom], p, trace)
+        hbm = None
+    if p.y0_csr is not None and roof is not None:
         roof["traffic"] = _pmc_traffic(f"{dom}_{PMC_TAGS.get(args.config, p.name)}", kernel_sources(dom)) \
             if dom in SPMM_KERNELS else None
         hbm = hbm_fields(roof, roof["traffic"])

@@ -162,3 +162,24 @@ def test_kernel_split_and_roofline_from_profile_records():
     assert hbm["effective"] == pytest.approx(want_bytes / 3e-3 / 1e9, abs=0.051)
     assert hbm["counter"] == pytest.approx(2 * want_bytes / 3e-3 / 1e9, abs=0.051)
     assert bench.hbm_fields(roof, None)["counter"] is None
+
+
+def test_forward_roofline_of_a_dense_batch():
+    """A dense forward's roofline is the timed forward's own, not that of the launches the profiling log makes of it: bytes
+    of the batch, the weights, the pointers and the biases over its time."""
+    from workloads import Layer, Problem
+    import numpy as np
+
+    n, batch = 1000, 64
+    layers = [Layer(np.zeros(n + 1, np.int64), np.zeros(0, np.int32), np.zeros(0, np.float32),
+                    np.zeros(n, np.float32)) for _ in range(3)]
+    for l in layers:
+        l.row_ptr[-1] = 4000
+    p = Problem("t", n, 3, batch, math.inf, layers)
+    roof = bench.forward_roofline(p, 0.02, 50)
+    want = 8 * n * batch + 3 * (8 * 4000 + 8 * (n + 1) + 4 * n)
+    assert roof["algorithmic_bytes_per_launch"] == want and roof["algorithmic_flops_per_launch"] == 6.0 * batch * 4000
+    assert roof["kernel"] == "forward" and roof["launches"] == 50 and roof["avg_launch_ms"] == 0.02
+    assert roof["bound"] == "hbm" and roof["achieved"] == pytest.approx(want / 2e-5 / 1e9, abs=0.051)
+    assert roof["frac"] == pytest.approx(roof["achieved"] / roof["peak"], abs=1e-4)
+    assert bench.hbm_fields(roof, None)["kernel"] == "forward"
