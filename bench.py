@@ -706,6 +706,12 @@ def summarize_counters(dirs, title, commands, out, longest=False):
         if m.get("SQ_VALU_MFMA_BUSY_CYCLES"):
             derived.append(f"| {k} | MFMA busy: SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x cycles) | "
                            f"{m['SQ_VALU_MFMA_BUSY_CYCLES'] / (1024 * cyc):.3f} |")
+        if m.get("SQ_LDS_IDX_ACTIVE"):
+            derived.append(f"| {k} | LDS busy: SQ_LDS_IDX_ACTIVE / (256 CUs x cycles) | "
+                           f"{m['SQ_LDS_IDX_ACTIVE'] / (256 * cyc):.3f} |")
+            if "SQ_LDS_BANK_CONFLICT" in m:
+                derived.append(f"| {k} | of that bank conflicts: SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE | "
+                               f"{m['SQ_LDS_BANK_CONFLICT'] / m['SQ_LDS_IDX_ACTIVE']:.3f} |")
         for c in ("TA_TA_BUSY_sum", "TD_TD_BUSY_sum"):
             if c in m:
                 derived.append(f"| {k} | {c} / (256 CUs x cycles) | {m[c] / (256 * cyc):.3f} |")
