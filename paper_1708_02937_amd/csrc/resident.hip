@@ -231,11 +231,11 @@ struct Slice {
     float4 w[kAhead];
 };
 
-// grid: (sample groups from sample `base` on, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
+// grid: (sample groups, neuron parts).  A part is `runs` consecutive runs of kRunLen neurons; with more than one
 // part (a single layer then) every part's workgroup reads all input rows and writes its own neurons.
 template <int V, class Op>
 __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs args, int layers, int n, int64_t batch,
-                                                                  int64_t base, int nslices, int runs, double ymax,
+                                                                  int nslices, int runs, double ymax,
                                                                   ResidentIo io) {
     using Row = typename RowOf<V>::T;
     extern __shared__ __align__(16) char resident_lds[];
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kRThreads) void spmm_resident_kernel(ResidentArgs a
     Row *dst = src + (n + 1);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t r0 = base + (int64_t)blockIdx.x * V;
+    const int64_t r0 = (int64_t)blockIdx.x * V;
     const int rows = (int)(batch - r0 < V ? batch - r0 : V);
     const int run0 = blockIdx.y * runs;
     const int run1 = min(run0 + runs, (nslices + kRunSlices - 1) / kRunSlices);
@@ -488,8 +488,19 @@ hipError_t launch_v(const ResidentArgs &args, int layers, int64_t n, int64_t bat
     const int64_t groups = (batch + V - 1) / V;
     const int64_t seg = (int64_t(1) << 21) / parts;  // groups per launch: fewer than 2^32 work-items
     for (int64_t g0 = 0; g0 < groups; g0 += seg) {
+        const int64_t r0 = g0 * V;  // the launch's first sample: everything indexed by sample starts there
+        ResidentIo part = io;
+        if (io.y_in) part.y_in += r0 * n;
+        if (io.row_ptr) part.row_ptr += r0;
+        if (io.cnt_in) {
+            part.cnt_in += r0;
+            part.col += r0 * n;
+            part.val += r0 * n;
+        }
+        part.y_out += r0 * n;
+        if (io.cnt_out) part.cnt_out += r0;
         spmm_resident_kernel<V, Op><<<dim3((unsigned)std::min(seg, groups - g0), (unsigned)parts), kRThreads, lds, s>>>(
-            args, layers, (int)n, batch, g0 * V, (int)((n + 63) / 64), per, ymax, io);
+            args, layers, (int)n, batch - r0, (int)((n + 63) / 64), per, ymax, part);
         const hipError_t el = hipGetLastError();
         if (el != hipSuccess) return el;
     }
