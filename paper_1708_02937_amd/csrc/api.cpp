@@ -327,8 +327,8 @@ struct ResidentPlan {
 // The rule, in microseconds measured on MI355X (n 300 to 5000, 16 to 819 entries per neuron, batch 33 to 2048).
 // A workgroup takes 0.015, 0.0163 or 0.0238 us per block of 4 x 64 entries at 1, 2 or 4 samples, a CU gets through
 // one workgroup's blocks at a time, a layer costs 0.85 us per run of 1024 neurons beyond that (n 4097, 12 entries,
-// batch 1, four layers: 33.8 us), a launch 2 to 3 us, and its rows in and out 0.12 per 1024 neurons and sample: once for
-// a fused range, in every round of workgroups where each layer is a launch.
+// batch 1, four layers: 33.8 us), a launch 2 to 3 us, and its rows in and out 0.12 per 1024 neurons and sample, in every
+// round of workgroups where the neurons are split.
 // So few samples per workgroup where that still fills the CUs once, four where the batch does so several times
 // over, and the neurons split over workgroups (then a launch per layer) where a small batch leaves CUs idle: one
 // layer of 4096 neurons and 64 entries each at batch 64 takes 23.7 us whole and 9.2 in four parts, four layers of
@@ -338,7 +338,8 @@ struct ResidentPlan {
 // product of high fan-in layers takes 1.76 + 1.21 density us per tile of 16 inputs and round of workgroups (64 neurons
 // x 256 samples): 157 us per layer at n 1000, batch 129, where the resident product takes 40.
 // A few long lists bound both: the wave that walks them in the resident product takes 0.095, 0.113 or 0.142 us per block
-// by itself (two workgroups share a CU at 1 and 2 samples where their LDS fits) and 0.6 of the even share beside it, and
+// by itself and 0.15 of the even share beside it, or 0.65 where two workgroups share a CU (at 1 and 2 samples, where their
+// LDS fits), and
 // the gather 0.055 to 0.11 us per entry beyond the mean, once per layer whatever the batch.  One list of 1459 entries in 2918 neurons,
 // batch 3045, four layers: 617 us at two samples per workgroup, 670 at four, 605 by the gather; one of 2048 in 4096,
 // batch 1024: 292, 308 and 603.
@@ -351,6 +352,12 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
     const double cus = (double)net->num_cu, size = (double)n, samples = (double)batch;
     const int64_t ld = sdnn::act_ld(n, batch);
     double gather = 6.0 + 4e-6 * size * samples;
+    // the gather's us per list entry: whole chunks of 256 samples, each on its own XCDs when there are 1, 2, 4 or 8
+    const int64_t chunks = (batch + 255) / 256;
+    const bool apart = chunks <= 8 && (chunks & (chunks - 1)) == 0;
+    const double per_entry = batch <= 252        ? samples * (n >= 4096 ? 1 / 4.1e6 : 1 / 3.0e6)
+                             : apart || n <= 1024 ? (double)chunks * (256.0 / 6.75e6)
+                                                  : (double)chunks * (256.0 / 4.5e6);
     for (int32_t k = k0; k < k1; ++k) {
         const Layer &l = net->layers[(size_t)k];
         const double nnz = (double)l.nnz;
@@ -367,41 +374,44 @@ bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch,
             const double entry = batch <= 252 ? (n >= 4096 ? 0.085 : 0.055)
                                  : n > 4096   ? 0.11
                                  : batch <= 1100 ? 0.068 : 0.1 - 0.045 * longest / size;
-            const int64_t chunks = (batch + 255) / 256;  // a power of two up to 8 keeps each on its own XCDs
-            const double rate = chunks <= 8 && 8 % chunks == 0 ? 6.75e6 : n > 1024 ? 4.5e6 : 6.75e6;
-            gather += 6.0 + nnz * (batch > 252 ? 256.0 * (double)chunks / rate : samples / (n >= 4096 ? 4.1e6 : 3.0e6)) +
-                      entry * std::max(0.0, longest - nnz / size);
+            gather += 6.0 + nnz * per_entry + entry * std::max(0.0, longest - nnz / size);
         }
     }
     const int64_t runs = (n + 1023) / 1024;
     const double layers = (double)(k1 - k0);
     const double per_block[] = {0.015, 0.0163, 0.0238}, alone[] = {0.095, 0.113, 0.142};
+    const double cu_share = 1.0 / cus, run_share = 1.0 / (double)runs;
     auto up = [](double x) {  // the next whole number
         const double whole = (double)(int64_t)x;
-        return whole < x ? whole + 1.0 : whole;
+        return whole + 1e-9 < x ? whole + 1.0 : whole;
     };
+    const int32_t most_parts = may_split ? (int32_t)runs : 1;
     double best = 0.0;
     for (int i = 0; i < 3; ++i) {
         const int v = 1 << i;
         const int64_t groups = (batch + v - 1) >> i;
-        for (int32_t parts = 1; parts <= (may_split ? (int32_t)runs : 1); ++parts) {
-            const int32_t per = ((int32_t)runs + parts - 1) / parts;  // runs of a part
-            const double workgroups = (double)(groups * (((int32_t)runs + per - 1) / per));
+        for (int32_t parts = 1; parts <= most_parts; ++parts) {
+            const int32_t per = parts == 1 ? (int32_t)runs : ((int32_t)runs + parts - 1) / parts;  // runs of a part
+            const double workgroups = (double)(groups * (parts == 1 ? 1 : ((int32_t)runs + per - 1) / per));
             const bool two = v < 4 && sdnn::resident_lds(n, v, parts == 1 ? n + 1 : per * 1024) <= sdnn::kResidentLds / 2;
-            const double load = std::max(1.0, workgroups / cus);
+            const double load = std::max(1.0, workgroups * cu_share);
             const double rounds = up(load), turns = two ? up(0.5 * load) : rounds;
-            const double block = per_block[i] * (double)per / (double)runs;
+            const double block = per_block[i] * (double)per * run_share;
+            const double beside = (two && load > 1.0 ? 0.65 : 0.15) * rounds;
             double t = 0.0;
             for (int32_t k = k0; k < k1; ++k) {
                 const Layer &l = net->layers[(size_t)k];
                 const double blocks = (double)l.resident_blocks * block;
                 const double wave = (double)std::min(l.resident_wave, (l.max_fanin + 3) / 4 * per);
                 t += std::max(rounds * blocks + 0.5 * (rounds - 1.0),
-                              turns * alone[i] * wave + 0.6 * load * blocks + 0.5 * (turns - 1.0));
+                              turns * alone[i] * wave + beside * blocks + 0.5 * (turns - 1.0));
             }
             const bool fused = parts == 1 && (semiring || !net->profiling);
             const double rows = 0.12 * (double)(runs << i);
-            t += fused ? 2.0 + rows + 0.85 * (double)runs * layers : (3.0 + rounds * (rows + 0.85 * (double)per)) * layers;
+            if (parts == 1)
+                t += (fused ? 1.0 : layers) * (2.0 + rows) + 0.85 * (double)runs * layers;
+            else
+                t += (3.0 + rounds * (rows + 0.85 * (double)per)) * layers;
             if (plan->v == 0 || t < 0.98 * best) {  // near ties: fewer samples and parts
                 best = t;
                 plan->v = v;

@@ -9,7 +9,7 @@ from workloads import Problem
 
 pytestmark = pytest.mark.gpu
 
-N, CHUNK = 128, 1 << 21
+N, CHUNK = 256, 1 << 21
 
 
 def _net(sd):
