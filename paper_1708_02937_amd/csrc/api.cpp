@@ -324,7 +324,8 @@ struct ResidentPlan {
     bool fused = true;
 };
 
-// The rule, in microseconds measured on MI355X (n 300 to 5000, 16 to 819 entries per neuron, batch 33 to 2048).
+// The rule, in microseconds measured on MI355X (n 150 to 5000, 4 to 1200 entries per neuron, batch 1 to 3045; within 10%
+// at 13 sizes with every number of samples and parts).
 // A workgroup takes 0.015, 0.0163 or 0.0238 us per block of 4 x 64 entries at 1, 2 or 4 samples, a CU gets through
 // one workgroup's blocks at a time, a layer costs 0.85 us per run of 1024 neurons beyond that (n 4097, 12 entries,
 // batch 1, four layers: 33.8 us), a launch 2 to 3 us, and its rows in and out 0.12 per 1024 neurons and sample, in every
@@ -338,13 +339,12 @@ struct ResidentPlan {
 // product of high fan-in layers takes 1.76 + 1.21 density us per tile of 16 inputs and round of workgroups (64 neurons
 // x 256 samples): 157 us per layer at n 1000, batch 129, where the resident product takes 40.
 // A few long lists bound both: the wave that walks them in the resident product takes 0.095, 0.113 or 0.142 us per block
-// by itself and 0.15 of the even share beside it, or 0.65 where two workgroups share a CU (at 1 and 2 samples, where their
-// LDS fits), and
-// the gather 0.055 to 0.11 us per entry beyond the mean, once per layer whatever the batch.  One list of 1459 entries in 2918 neurons,
-// batch 3045, four layers: 617 us at two samples per workgroup, 670 at four, 605 by the gather; one of 2048 in 4096,
-// batch 1024: 292, 308 and 603.
-// With profiling on every layer is a launch of its own, and ranges with a
-// layer of under 2^24 products stay on the neuron-major products: the one launch is what they gain from.
+// by itself and 0.15 of the even share beside it, or 0.65 where two workgroups share a CU (at 1 and 2 samples, where
+// their LDS fits), and the gather 0.055 to 0.11 us per entry beyond the mean, once per layer whatever the batch.  One
+// list of 1459 entries in 2918 neurons, batch 3045, four layers: 617 us at two samples per workgroup, 670 at four, 605 by
+// the gather; one of 2048 in 4096, batch 1024: 292, 308 and 603.
+// With profiling on every layer is a launch of its own, and ranges with a layer of under 2^24 products stay on the
+// neuron-major products: the one launch is what they gain from.
 bool plan_resident(const sdnn_net_s *net, int32_t k0, int32_t k1, int64_t batch, bool may_split, bool semiring,
                    ResidentPlan *plan) {
     const int64_t n = net->n;
@@ -1070,7 +1070,7 @@ sdnn_status sdnn_forward_csr(sdnn_net net, int32_t k0, int32_t k1, int64_t batch
         SDNN_HIP(prof_end(net, pr));
         int dc = 0;
         // the last product counts its nonzeros for the packing, into the value buffer the packed rows go to (at least
-        // n * round64(batch) floats, an eighth of it used; free until then)
+        // n * batch floats, a thirty-second of it used: n * batch / 8 bytes; free until then)
         uint8_t *counts = net->layers[(size_t)(k1 - 1)].regions ? reinterpret_cast<uint8_t *>(w.val[db ^ 1]) : nullptr;
         for (int32_t k = kd; k < k1; ++k) {
             const Layer &l = net->layers[(size_t)k];

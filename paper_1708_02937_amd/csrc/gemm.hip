@@ -22,10 +22,11 @@
 // blocks of 16 x 16 MFMAs.  Two workgroups share a CU (80 KiB of LDS each in fp64), so one's barrier and LDS waits are
 // covered by the other's MFMAs.  K advances 32 at a time through double-buffered LDS (one barrier per step): the next
 // slab is loaded into registers ahead of the current one's products and stored into the other buffer after them.
-// MFMA-bound: the matrix cores are busy 82% of a workgroup's time at 2.27 GHz (fp32).  Measured on MI355X against
+// MFMA-bound: the matrix cores are busy 78% (fp32) and 82% (fp64) of a launch at n 4096, batch 1024.  Measured on MI355X against
 // k-major operands read 4 or 8 bytes per lane, 4 waves of 64 x 32, guarded element loads at ragged sizes (us per
 // forward, before -> after): n 4096 batch 1024 L 2 fp32 603 -> 567, fp64 1069 -> 1069; n 1236 batch 906 L 2 fp32 198 ->
-// 95; n 3001 batch 1001 fp64 526 -> 316; n 4096 batch 64 fp32 38.8 -> 34.9, fp64 52.6 -> 53.8.  Not kept: four waves of
+// 95; n 3001 batch 1001 fp64 526 -> 316; n 4096 batch 64 fp32 38.8 -> 34.9, fp64 53.5 -> 54.6 (with K split, n 1024 batch 512 to n 4096 batch
+// 128 it is 2 to 4% above at a few sizes, in the product itself).  Not kept: four waves of
 // 64 x 32 (fp64 1093), fragments read a part ahead with the barrier between the parts (fp32 571-582, fp64 1129-1157),
 // 32 x 32 x 2 fp32 MFMAs (590), raised wave priority around the MFMAs (570), K steps of 16 in fp64 (1075).
 //

@@ -1,20 +1,22 @@
 // Dense-Y forward with the activations of a few samples resident in LDS (Sec. III batched inference equation;
-// Sec. IV loop body), for layers of at most 5119 neurons.
+// Sec. IV loop body), for layers of at most 5119 neurons.  (Layers of 4097 neurons on with short lists at batch 256 and
+// more run on the sample-blocked layout, whose choice is made first.)
 //
 // A workgroup (16 wave64s, one per CU) owns V samples (4, 2 or 1) and keeps all n activations of them in LDS as
 // rows of V floats, one row per neuron; a lane owns one output neuron, walks its fan-in list in ascending input
 // order, reads the input's row (one LDS read of V floats) and adds the V exact products to its fp64 sums (or folds
-// them over another semiring of Sec. II, one layer without bias and activation).  The bias, h and the rounding follow, and the outputs form the next layer's rows in a second LDS buffer, so a whole
-// range of layers is one launch: the batch is read once, batch-major, and written once, and nothing else of it
-// touches memory.
+// them over another semiring of Sec. II, one layer without bias and activation).  The bias, h and the rounding follow,
+// and the outputs form the next layer's rows in a second LDS buffer, so a whole range of layers is one launch: the
+// batch is read once, batch-major, and written once, and nothing else of it touches memory.
 //
 // What bounds it: at V = 4 LDS (64 lanes reading random 16-byte rows; the LDS pipe is busy 75% of the time, two
 // thirds of that bank conflicts) and VALU issue (44 instructions per block of 4 x 64 entries, 36 of them the
-// conversions and fp64 multiply-adds) together; below that the list stream from L2.  The neuron-major gather it
-// replaces at these widths moves 4 bytes per product through the L1 from L2, and pays two transposes and a launch
-// per layer.  Measured on MI355X (before -> after): n 4096, two layers of 10%, batch 1024 490 -> 343 us; four
+// conversions and fp64 multiply-adds, issuing 75-80% of the time) together; below that the list stream from L2.  The
+// neuron-major gather it replaces at these widths moves 4 bytes per product through the L1 from L2, and pays two
+// transposes and a launch per layer.  Measured on MI355X (before -> after): n 4096, two layers of 10%, batch 1024 490 -> 343 us; four
 // layers of 1%, batch 1021 262 -> 88 us; n 2999, six layers of 32 entries, batch 777 282 -> 82 us; n 1024, four
-// layers of 16 entries, batch 64 25.3 -> 11.5 us.  Lists two, three or four blocks ahead: 363, 352, 351 us on the
+// layers of 16 entries, batch 64 25.3 -> 11.5 us (on lists used before: the first call on a net is 36.5 against 49.5
+// us for the last, and one layer of 4096 neurons, 64 entries, batch 64 37.5 against 39.7, 9.6 against 17.2 later).  Lists two, three or four blocks ahead: 363, 352, 351 us on the
 // first of these, 80.8, 81.9, 83.2 on the third.
 //
 // Lists.  Set-up sorts each run of 1024 neurons by list length and cuts it into 16 slices of 64 (one lane per
