@@ -7,6 +7,8 @@
 // of the entries by column (8-bit digits: tile histograms, a scan per digit, a stable scatter), which
 // leaves every list in ascending input order, so the stored order, and with it the fp64 summation order of
 // the forward pass, does not depend on atomic timing.  List pointers come from a column count and a scan.
+#include <algorithm>
+
 #include "common.h"
 
 namespace sdnn {
@@ -279,11 +281,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int64_t nnz,
     }
 }
 
-__global__ void max_segment_kernel(int64_t n, const int64_t *__restrict__ ptr, int32_t *out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t len = i < n ? (int32_t)(ptr[i + 1] - ptr[i]) : 0;
+// Longest segment: one atomic per workgroup, of which there are at most kMaxSegmentBlocks (one per wave queues on the
+// one address: 0.2 ms for 2^20 rows).
+constexpr int kMaxSegmentBlocks = 1024;
+
+__global__ __launch_bounds__(256) void max_segment_kernel(int64_t n, const int64_t *__restrict__ ptr, int32_t *out) {
+    __shared__ int32_t waves[4];
+    int32_t len = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        len = max(len, (int32_t)(ptr[i + 1] - ptr[i]));
     for (int d = 32; d > 0; d >>= 1) len = max(len, __shfl_xor(len, d));
-    if (threadIdx.x % 64 == 0) atomicMax(out, len);
+    if (threadIdx.x % 64 == 0) waves[threadIdx.x / 64] = len;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(out, max(max(waves[0], waves[1]), max(waves[2], waves[3])));
 }
 
 __global__ void pack_edges_kernel(int64_t nnz, const int32_t *__restrict__ col, const float *__restrict__ val,
@@ -389,7 +399,7 @@ hipError_t launch_exclusive_scan_i32_to_i64(int64_t count, const int32_t *in, in
 }
 
 hipError_t launch_max_segment(int64_t n, const int64_t *ptr, int32_t *out, hipStream_t s) {
-    max_segment_kernel<<<blocks_for(n, 256), 256, 0, s>>>(n, ptr, out);
+    max_segment_kernel<<<std::min<unsigned>(blocks_for(n, 256), kMaxSegmentBlocks), 256, 0, s>>>(n, ptr, out);
     return hipGetLastError();
 }
 
