@@ -622,7 +622,7 @@ def summarize_stats(csv_dir, title, command, out):
 
     path = sorted(glob.glob(os.path.join(csv_dir, "**", "*kernel_stats.csv"), recursive=True))[0]
     rows = list(csv.DictReader(open(path)))
-    lines = ["# rocprofv3 kernel statistics", "", "command (from the repository root on the MI355X box):", "",
+    lines = ["# rocprofv3 kernel statistics", "", "command (from the repository root, on an MI355X):", "",
              f"    {command}", "", title, "", "| kernel | calls | avg us | min us | max us | share % |",
              "|---|---|---|---|---|---|"]
     for r in rows:
@@ -656,7 +656,7 @@ def summarize_pmc(kernel, tag, dirs, copy_bytes, commands, out, src_names):
              f"FETCH_SIZE and WRITE_SIZE (KiB per dispatch), averaged over {nf} / {nw} dispatches of the kernel,",
              f"each scaled by what the same counter reads for a plain device copy of {copy_bytes} bytes",
              f"(rocclr copyBuffer: FETCH_SIZE {cfetch:.1f} KiB -> scale {fs:.3f}; WRITE_SIZE {cwrite:.1f} KiB -> "
-             f"scale {ws:.3f}).", "", "commands (from the repository root on the MI355X box):", ""]
+             f"scale {ws:.3f}).", "", "commands (from the repository root, on an MI355X):", ""]
     lines += [f"    {c}" for c in commands]
     lines += ["", f"workload: {tag}", f"fetch_kib_per_dispatch: {fetch:.1f}", f"write_kib_per_dispatch: {write:.1f}",
               f"fetch_scale: {fs:.4f}", f"write_scale: {ws:.4f}", f"hbm_bytes_per_launch: {hbm}",
@@ -689,7 +689,7 @@ def summarize_counters(dirs, title, commands, out, longest=False):
                 rows = [r for r in rows if dur[_short_name(r["Kernel_Name"])][1] == r["Dispatch_Id"]]
             for r in rows:
                 agg[_short_name(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
-    lines = [f"# rocprofv3 counters: {title}", "", "commands (from the repository root on the MI355X box):", ""]
+    lines = [f"# rocprofv3 counters: {title}", "", "commands (from the repository root, on an MI355X):", ""]
     lines += [f"    {c}" for c in commands]
     lines += ["", "| kernel | counter | dispatches | mean per dispatch |", "|---|---|---|---|"]
     derived = []
